@@ -434,6 +434,19 @@ __device__ __forceinline__ void poly_coeffs(const float (&ur)[L], const float (&
     }
 }
 
+// c_1 alone, summed as poly_coeffs sums it.
+template <int L>
+__device__ __forceinline__ void lag1_coeff(const float (&ur)[L], const float (&ui)[L], float& c1r, float& c1i) {
+    float sr = 0.f, si = 0.f;
+#pragma unroll
+    for (int i = 0; i + 1 < L; ++i) {
+        sr = fmaf(ur[i], ur[i + 1], fmaf(ui[i], ui[i + 1], sr));
+        si = fmaf(ui[i], ur[i + 1], fmaf(-ur[i], ui[i + 1], si));
+    }
+    c1r = -sr;
+    c1i = -si;
+}
+
 // Newton iterations on the quadratic factor z^2 - r z - s of the polynomial
 // (complex Bairstow), in precision T: at most `iters` steps, fewer once a
 // step is below tol |r|.  Returns false when a step is not finite; `lastc`
@@ -853,6 +866,51 @@ __device__ __forceinline__ bool certified_root(const float (&ar)[2 * L - 1], con
     }
 }
 
+// A window that is close to one tone needs no division and no root count.
+// Write v = cos(th) a(w) + sin(th) d with a(w) the unit steering vector (real
+// form) of the peak w and d a unit vector orthogonal to it, s = sin(th) =
+// sqrt(dep / L).  On z = e^{j(w + x + j tau)} the polynomial is
+// z^{L-1} L (1 - (cos(th) D + s h)^2), D the Dirichlet kernel sum_i cos(s_i
+// (x + j tau)) / L and h = d^T a(w + x + j tau), |h| <= H (the largest value
+// over real unit d, from D and the steering vector's own 2 x 2 Gram matrix).
+// Against the noise-free polynomial, L (1 - D^2), which has a double root at
+// e^{jw} and every other root inside |z| < 0.58 or outside its inverse
+// (L <= 8; 0.78 at L = 17), the difference on the circle |z| = kappa =
+// e^{-tau} is at most L (2 s cos(th) |D| H + s^2 (H^2 + |D|^2)); where that is
+// below L |1 - D^2| for every x, Rouche's theorem (on |z| = kappa and its
+// mirror 1/kappa) leaves exactly two roots, one pair, in the annulus between
+// them.  So a root pair found in the annulus is the only one there, and every
+// other pair is farther from the circle: it is the pair the selection rule
+// takes.  The largest s that holds at the best kappa, and that kappa, per L
+// (evaluated on a fine grid of x): s^2 = 0.0623 at L = 3, 0.0727-0.0760 for
+// L = 4 .. 17; the tests use 0.055 and 0.065.  Windows at 10 dB have s^2 of
+// 2e-4 at the median and 1.5e-3 at most (L = 6, 8, N = 32), at 6 dB with
+// N = 16, L = 4 0.09 at most, so nearly all pass, and what it saves is the
+// polynomial's coefficients, the division and the Schur-Cohn count: 16 frames
+// of 4096 x 4096 (L = 8, N = 32) 30.40 -> 21.75 ms, 100 of 1024 x 1024 (L = 6)
+// 8.72 -> 7.16, 20 of 1024 x 1024 with 11 x 11 blocks 6.76 -> 4.75.
+constexpr float tone_s2(int L) { return L == 3 ? 0.055f : 0.065f; }
+constexpr float tone_kappa(int L) {
+    return L <= 3 ? 0.40f : L == 4 ? 0.46f : L == 5 ? 0.53f : L == 6 ? 0.59f : L == 7 ? 0.63f : L == 8 ? 0.67f
+         : L == 9 ? 0.70f : L <= 11 ? 0.75f : L <= 13 ? 0.78f : L <= 15 ? 0.81f : 0.83f;
+}
+
+// True when z, a point where pair_newton's stop rule was met, belongs to the
+// pair nearest the unit circle by the argument above.  A step below 1e-4 |z|
+// and below 1e-2 |z - 1/conj z| puts a root of the polynomial within (2L - 2)
+// 1.01e-4 |z| of the point it was taken from (the sum of the 2L - 2
+// reciprocal distances, less the mate's, is the step's reciprocal), hence the
+// 0.01 kept to the annulus' edge.  A point within 1e-9 of the circle (a root
+// that is its own mirror) is refused, as certified_root does.
+template <int L>
+__device__ __forceinline__ bool tone_pair(double zr, double zi, float dep) {
+    if constexpr (L < 3) return false;
+    constexpr float k2 = (tone_kappa(L) + 0.01f) * (tone_kappa(L) + 0.01f);
+    const double m2 = fma(zr, zr, zi * zi);
+    const float r2 = (float)m2;
+    return dep <= tone_s2(L) * (float)L && r2 >= k2 && r2 <= 1.f / k2 && fabs(m2 - 1.0) > 2.5e-9;
+}
+
 // Direction of the frequency guess from the lag-1 coefficient: u1[i+1]/u1[i]
 // ~ e^{j w}, so c_1 ~ -((L-1)/L) e^{-j w} and e^{j w} = -conj(c_1) / |c_1|
 // (no trigonometric functions needed); (1, 0) when c_1 vanishes.
@@ -913,8 +971,11 @@ __device__ __forceinline__ void spectral_g(const float (&v)[L], float hc, float 
 // slowest lane 2.9 -> 1.0, FP64 1.7 -> 1.0, against the lag-1 direction at a
 // radius fitted to lambda_1 and K).  Any start is safe: the certificate
 // judges the root found.
+// `dep` receives L - g(w)^2 = L sin^2 of the angle between v and the steering
+// vector of the peak w: what tone_pair judges the window by.
 template <int L>
-__device__ __forceinline__ void pair_start(const float (&v)[L], float cw, float sw, double& zr, double& zi) {
+__device__ __forceinline__ void pair_start(const float (&v)[L], float cw, float sw, double& zr, double& zi,
+                                           float& dep) {
     // e^{j w/2} from e^{j w} (cos(w/2) >= 0)
     float hc = fsqrt(fmaxf(0.5f * (1.f + cw), 0.f));
     float hs = hc > 1e-3f ? 0.5f * sw * frcp(hc) : 1.f;
@@ -931,7 +992,7 @@ __device__ __forceinline__ void pair_start(const float (&v)[L], float cw, float 
     const float nc = hc * rc - hs * rs, ns = hs * rc + hc * rs;
     spectral_g<L>(v, nc, ns, g, g1, g2);
     const float hh = fmaf(g1, g1, g * g2);
-    const float dep = fmaxf((float)L - g * g, 0.f);
+    dep = fmaxf((float)L - g * g, 0.f);
     float t = hh < 0.f ? fsqrt(dep * frcp(-hh)) : 0.01f;
     t = fminf(0.1f, fmaxf(1e-4f, finitef(t) ? t : 0.01f));
     const float r0 = __expf(-t);
@@ -1385,27 +1446,44 @@ __device__ __forceinline__ void window_omega_v(const float (&v)[L], const RootTe
     constexpr int n = 2 * L - 2;
     float ur[L], ui[L];
     signal_vector<L>(v, ur, ui);
-    // ---- polynomial coefficients (Eq. 12-14) -----------------------------
-    float ar[n + 1], ai[n + 1];
-    poly_coeffs<L>(ur, ui, ar, ai);
-
     // frequency guess from the lag-1 coefficient c_1, or, with the temporal
     // warm start, the previous frame's frequency at this pixel
     float sw0, cw0;
-    if (finitef(wprev)) __sincosf(wprev, &sw0, &cw0);
-    else guess_direction(ar[L], ai[L], cw0, sw0);
+    if (finitef(wprev)) {
+        __sincosf(wprev, &sw0, &cw0);
+    } else {
+        float c1r, c1i;
+        lag1_coeff<L>(ur, ui, c1r, c1i);
+        guess_direction(c1r, c1i, cw0, sw0);
+    }
 
     // ---- certified pair ---------------------------------------------------
     // FP64 Newton (with the mate divided out) for the signal root from the
     // guess w0; when its pair is certified as the pair nearest the unit
     // circle it is the pair the selection rule picks from all roots, and its
     // sum gives omega exactly as below.  Otherwise every root is found.
-    bool cert = false;
+    double zr0 = 0.0, zi0 = 0.0;
+    bool root = false;
     if (!full_roots) {
-        double zr0, zi0, rr = 0.0, ri = 0.0;
-        pair_start<L>(v, cw0, sw0, zr0, zi0);
+        float dep;
+        pair_start<L>(v, cw0, sw0, zr0, zi0, dep);
         pair_newton32<L>(ur, ui, zr0, zi0, kCertIters32, &ls.pair_its32);
-        cert = pair_newton<L>(ur, ui, zr0, zi0, kCertIters, &ls.pair_its) && certified_root<L>(ar, ai, zr0, zi0, rr, ri);
+        root = pair_newton<L>(ur, ui, zr0, zi0, kCertIters, &ls.pair_its);
+        if (root && tone_pair<L>(zr0, zi0, dep)) {
+            // z + 1/conj(z) = z (1 + 1/|z|^2): the pair's sum has z's own angle
+            omega = atan2f((float)zi0, (float)zr0);
+            ls.accepted += 1;
+            return;
+        }
+    }
+
+    // ---- polynomial coefficients (Eq. 12-14) -----------------------------
+    float ar[n + 1], ai[n + 1];
+    poly_coeffs<L>(ur, ui, ar, ai);
+    bool cert = false;
+    if (root) {
+        double rr = 0.0, ri = 0.0;
+        cert = certified_root<L>(ar, ai, zr0, zi0, rr, ri);
         if (cert) omega = atan2f((float)ri, (float)rr);
     }
     ls.accepted += cert ? 1 : 0;
