@@ -1251,8 +1251,24 @@ __device__ __forceinline__ void T_from_snapshots(int K, F snap, Sym<L>& T, float
 // lambda_1 > lambda_2 (1 + 1e-5), so an accepted window is never degenerate.  Returns false (v undefined) when no step
 // within max_steps is accepted; *steps counts the steps taken.  *nu receives
 // the MUSIC null spectrum 1 - (v^T v0)^2 at the prediction.
+//
+// The iteration runs on T - mu I, mu = (1 - sqrt(tr T^2)) / (L - 1): with one
+// large eigenvalue, lambda_1 is nearly sqrt(tr T^2) and mu the mean of the
+// others (the trace is 1).  The noise eigenvalues then lie about zero instead
+// of between zero and their largest, so a step contracts the angle about twice
+// as much and l2 is their spread.  The eigenvectors and the residual are T's
+// own, and everything above holds with rho, l2 and tr T^2 of the shifted
+// matrix, for any mu (the gap is compared with the unshifted rho).  The FP32
+// rounding of tr T^2 - rho^2 is added to it.  Numpy trials: steps of a wave's
+// slowest lane 3.7 -> 3.2 at 10 dB (L = 6, 8; N = 32), 5.2 -> 4.6 at 7 dB (L =
+// 8, N = 24), 7.1 -> 5.8 at 6 dB (L = 4, N = 16, where the windows that give up
+// fall from 2.7% to 0.4%), true angles of the accepted vectors 2.1e-6 -> 1.3e-6
+// rms; measured, 16 frames of 4096 x 4096 (L = 8) 21.75 -> 21.50 ms, the uneven
+// batch (5-20 dB) 6.96 -> 6.70, 20 frames with 11 x 11 blocks 4.75 -> 4.63.
+// T's diagonal is shifted in place, and shifted back when no step is accepted.
+constexpr float kPowerRound = 4e-7f;   // FP32 rounding of tr T^2 - rho^2, both at most 1
 template <int L>
-__device__ __forceinline__ bool power_top_eigvec(const Sym<L>& T, float hc, float hs, int min_steps, int max_steps,
+__device__ __forceinline__ bool power_top_eigvec(Sym<L>& T, float hc, float hs, int min_steps, int max_steps,
                                                  float tol, float (&v)[L], int& steps, float& nu) {
     constexpr int m = L / 2;
     constexpr int o = L - m;
@@ -1277,17 +1293,23 @@ __device__ __forceinline__ bool power_top_eigvec(const Sym<L>& T, float hc, floa
         }
         if (L & 1) v0[m] = frsq((float)L);
     }
-    float t2 = 0.f;                                         // tr T^2
+    float t2 = 0.f, off2 = 0.f;                             // tr T^2
 #pragma unroll
     for (int i = 0; i < L; ++i) {
         t2 = fmaf(T.a[i][i], T.a[i][i], t2);
 #pragma unroll
-        for (int j = i + 1; j < L; ++j) t2 = fmaf(2.f * T.a[i][j], T.a[i][j], t2);
+        for (int j = i + 1; j < L; ++j) off2 = fmaf(T.a[i][j], T.a[i][j], off2);
     }
+    t2 = fmaf(2.f, off2, t2);
+    const float mu = fmaxf(1.f - fsqrt(t2), 0.f) * (1.f / (float)(L - 1));
+    t2 = fmaf(fmaf((float)L, mu, -2.f), mu, t2) + kPowerRound;   // tr (T - mu I)^2
+#pragma unroll
+    for (int i = 0; i < L; ++i) T.a[i][i] -= mu;
 #pragma unroll
     for (int i = 0; i < L; ++i) v[i] = v0[i];
-    // Unnormalised steps: the trace is 1, so lambda_1 >= 1/L and max_steps
-    // steps shrink the iterate by at most L^-max_steps, far inside FP32's range.
+    // Unnormalised steps: the trace is 1, so the shifted lambda_1 stays above
+    // 1/L^2 and max_steps steps shrink the iterate by at most L^-(2 max_steps),
+    // inside FP32's range.
     bool ok = false;
     for (int it = 0; it < max_steps; ++it) {
         ++steps;
@@ -1314,20 +1336,23 @@ __device__ __forceinline__ bool power_top_eigvec(const Sym<L>& T, float hc, floa
                 const float r = fmaf(-rho, v[i], y[i]);
                 r2 = fmaf(r, r, r2);
             }
-            // |lambda_i| <= l2 for every i >= 2 (Frobenius), sin(theta) of v <= sb,
-            // and the step contracts tan(theta) by at least l2 / rho
-            const float l2 = fsqrt(fmaxf(fmaf(-rho, rho, t2), 0.f));
-            const float gap = rho - l2;
-            const float sb2 = r2 * ivv * frcp(gap * gap);
-            const float c2 = l2 * l2 * frcp(rho * rho);
-            ok = gap > kDegenRel * rho && sb2 <= 0.25f && sb2 * c2 * (4.f / 3.f) <= tol * tol && finitef(ivv);
+            // |lambda_i| <= l for every i >= 2 (Frobenius, ll = l^2), sin(theta) of v <= sb with
+            // sb^2 = sn / g2, and the step contracts tan(theta) by at least l / rho
+            const float ll = fmaxf(fmaf(-rho, rho, t2), kPowerRound);
+            const float gap = rho - fsqrt(ll);
+            const float g2 = gap * gap, sn = r2 * ivv;
+            ok = gap > kDegenRel * (rho + mu) && sn <= 0.25f * g2 &&
+                 sn * ll * (4.f / 3.f) <= tol * tol * g2 * rho * rho && finitef(ivv);
             // give up early where even the remaining steps at the proven
             // contraction cannot reach tol (low SNR: the plain solver is cheaper)
-            const float left = (float)(max_steps - it);
-            const bool hopeless = !(gap > 0.f) || !finitef(ivv) ||
-                                  fminf(sb2, 0.25f) * (4.f / 3.f) *
-                                          __builtin_amdgcn_exp2f(left * __builtin_amdgcn_logf(c2)) > tol * tol;
-            if (!ok && hopeless) break;
+            if (!ok) {
+                if (!(gap > 0.f) || !finitef(ivv)) break;
+                const float left = (float)(max_steps - it);
+                const float c2 = ll * frcp(rho * rho);
+                if (fminf(sn * frcp(g2), 0.25f) * (4.f / 3.f) *
+                        __builtin_amdgcn_exp2f(left * __builtin_amdgcn_logf(c2)) > tol * tol)
+                    break;
+            }
         }
 #pragma unroll
         for (int i = 0; i < L; ++i) v[i] = y[i];
@@ -1344,6 +1369,10 @@ __device__ __forceinline__ bool power_top_eigvec(const Sym<L>& T, float hc, floa
     for (int i = 0; i < L; ++i) v[i] *= in;
     dot *= in;
     nu = 1.f - dot * dot;
+    if (!ok) {
+#pragma unroll
+        for (int i = 0; i < L; ++i) T.a[i][i] += mu;
+    }
     return ok;
 }
 
