@@ -434,19 +434,6 @@ __device__ __forceinline__ void poly_coeffs(const float (&ur)[L], const float (&
     }
 }
 
-// c_1 alone, summed as poly_coeffs sums it.
-template <int L>
-__device__ __forceinline__ void lag1_coeff(const float (&ur)[L], const float (&ui)[L], float& c1r, float& c1i) {
-    float sr = 0.f, si = 0.f;
-#pragma unroll
-    for (int i = 0; i + 1 < L; ++i) {
-        sr = fmaf(ur[i], ur[i + 1], fmaf(ui[i], ui[i + 1], sr));
-        si = fmaf(ui[i], ur[i + 1], fmaf(-ur[i], ui[i + 1], si));
-    }
-    c1r = -sr;
-    c1i = -si;
-}
-
 // Newton iterations on the quadratic factor z^2 - r z - s of the polynomial
 // (complex Bairstow), in precision T: at most `iters` steps, fewer once a
 // step is below tol |r|.  Returns false when a step is not finite; `lastc`
@@ -886,40 +873,172 @@ __device__ __forceinline__ bool certified_root(const float (&ar)[2 * L - 1], con
 // L = 4 .. 17; the tests use 0.055 and 0.065.  Windows at 10 dB have s^2 of
 // 2e-4 at the median and 1.5e-3 at most (L = 6, 8, N = 32), at 6 dB with
 // N = 16, L = 4 0.09 at most, so nearly all pass, and what it saves is the
-// polynomial's coefficients, the division and the Schur-Cohn count: 16 frames
-// of 4096 x 4096 (L = 8, N = 32) 30.40 -> 21.75 ms, 100 of 1024 x 1024 (L = 6)
-// 8.72 -> 7.16, 20 of 1024 x 1024 with 11 x 11 blocks 6.76 -> 4.75.
+// polynomial's coefficients, the division and the Schur-Cohn count: with
+// Newton's root still, 16 frames of 4096 x 4096 (L = 8, N = 32) 30.40 -> 21.75
+// ms, 100 of 1024 x 1024 (L = 6) 8.72 -> 7.16, 20 of 1024 x 1024 with 11 x 11
+// blocks 6.76 -> 4.75.
+// (L = 2: every vector is a steering vector and there is one pair.)
 constexpr float tone_s2(int L) { return L == 3 ? 0.055f : 0.065f; }
 constexpr float tone_kappa(int L) {
     return L <= 3 ? 0.40f : L == 4 ? 0.46f : L == 5 ? 0.53f : L == 6 ? 0.59f : L == 7 ? 0.63f : L == 8 ? 0.67f
          : L == 9 ? 0.70f : L <= 11 ? 0.75f : L <= 13 ? 0.78f : L <= 15 ? 0.81f : 0.83f;
 }
 
-// True when z, a point where pair_newton's stop rule was met, belongs to the
-// pair nearest the unit circle by the argument above.  A step below 1e-4 |z|
-// and below 1e-2 |z - 1/conj z| puts a root of the polynomial within (2L - 2)
-// 1.01e-4 |z| of the point it was taken from (the sum of the 2L - 2
-// reciprocal distances, less the mate's, is the step's reciprocal), hence the
-// 0.01 kept to the annulus' edge.  A point within 1e-9 of the circle (a root
-// that is its own mirror) is refused, as certified_root does.
-template <int L>
-__device__ __forceinline__ bool tone_pair(double zr, double zi, float dep) {
-    if constexpr (L < 3) return false;
-    constexpr float k2 = (tone_kappa(L) + 0.01f) * (tone_kappa(L) + 0.01f);
-    const double m2 = fma(zr, zr, zi * zi);
-    const float r2 = (float)m2;
-    return dep <= tone_s2(L) * (float)L && r2 >= k2 && r2 <= 1.f / k2 && fabs(m2 - 1.0) > 2.5e-9;
-}
-
 // Direction of the frequency guess from the lag-1 coefficient: u1[i+1]/u1[i]
-// ~ e^{j w}, so c_1 ~ -((L-1)/L) e^{-j w} and e^{j w} = -conj(c_1) / |c_1|
-// (no trigonometric functions needed); (1, 0) when c_1 vanishes.
-__device__ __forceinline__ void guess_direction(float c1r, float c1i, float& cw, float& sw) {
-    const float m2 = c1r * c1r + c1i * c1i;
+// ~ e^{j w}, so S = sum_i u1[i] conj(u1[i+1]) = -c_1 ~ e^{-j w} and e^{j w} =
+// conj(S) / |S| (no trigonometric functions needed); (1, 0) when S vanishes.
+// u1 = Q v is conjugate-symmetric, so the terms i and L - 2 - i are equal: half
+// of them, with a_i = v_i + j v_{o+i} = sqrt2 u1[i], give a multiple of S.
+template <int L>
+__device__ __forceinline__ void guess_direction(const float (&v)[L], float& cw, float& sw) {
+    constexpr int m = L / 2;
+    constexpr int o = L - m;
+    constexpr float kSqrt2 = 1.41421356237309515f;
+    float sr = 0.f, si = 0.f;
+#pragma unroll
+    for (int i = 0; i + 1 < m; ++i) {
+        sr = fmaf(v[i], v[i + 1], fmaf(v[o + i], v[o + i + 1], sr));
+        si = fmaf(v[o + i], v[i + 1], fmaf(-v[i], v[o + i + 1], si));
+    }
+    const float xr = v[m - 1], xi = v[o + m - 1];
+    if (L & 1) {
+        sr = fmaf(kSqrt2 * v[m], xr, sr);
+        si = fmaf(kSqrt2 * v[m], xi, si);
+    } else {
+        sr = fmaf(0.5f * xr, xr, fmaf(-0.5f * xi, xi, sr));
+        si = fmaf(xr, xi, si);
+    }
+    const float m2 = sr * sr + si * si;
     const bool ok = m2 > 0.f && finitef(m2);
     const float im = ok ? frsq(m2) : 0.f;
-    cw = ok ? -c1r * im : 1.f;
-    sw = ok ? c1i * im : 0.f;
+    cw = ok ? sr * im : 1.f;
+    sw = ok ? -si * im : 0.f;
+}
+
+// omega of a window close to one tone: the root pair by the argument above, in
+// closed form.  On the unit circle g(w) = e^{-jw(L-1)/2} B(e^{jw}) is real, and
+// the roots of P(e^{j zeta}) = 0 are those of g(zeta)^2 = L.  With k_i =
+// (L-1)/2 - i, x_i = v_i cos(k_i w) - v_{o+i} sin(k_i w) and y_i = dx_i/dw / k_i,
+// the derivatives of g at w are moments of x and y,
+//   h_0 = sqrt2 sum x_i (+ v_m, L odd), h_1 = sqrt2 sum k_i y_i,
+//   h_2 = -sqrt2 sum k_i^2 x_i, h_3 = -sqrt2 sum k_i^3 y_i, ...
+// One Newton step a = -h_1/h_2 moves w to the peak of g (x and y rotated by
+// k_i a).  There the pair is at w + x +- j t, and with T = t^2
+//   Re g(w + j t) = h_0 - h_2 T/2 + h_4 T^2/24 = sqrt L (up to g's sign) gives T,
+//   Im g = 0: x = (h_3 T/6 - h_1 - h_5 T^2/120 - h_3 x^2/2) / (h_2 - h_4 T/6).
+// Only the angles k_i w need more than FP32: an error of theirs is an error of
+// omega, so e^{j k w} comes from FP64 products of the normalised guess and x
+// and y are formed in FP64 (FP32 leaves 1e-7 rad of the recurrence's rounding);
+// everything after is relative to the small a, x and T.  In numpy trials (L =
+// 2-8, 3-60 dB, FP32 where this code has it) omega is within 1e-9 rad of the
+// FP64 root at the 99.9th percentile, where Newton's iteration on P in FP64
+// stopped within 1e-8.  T below zero is a pair on the circle, which FP32
+// rounding of |v| makes of a double root there: the same formula gives the
+// mean angle of the two.  False (nothing written) when the window is not within
+// tone_s2 of a tone, the step to the peak is not small, the peak is not
+// reached to 3e-4 rad (beyond it the terms left out count), or k^2 T > 0.2
+// (beyond the series, and well inside the annulus).
+// Bound by VALU issue, so what counts is instructions: 40 in FP64 and about
+// 140 in FP32 at L = 8, against about 110 and 310 for the start, the FP32 and
+// FP64 Newton steps and their evaluations of P and P'.  Measured: 16 frames of
+// 4096 x 4096 (L = 8, N = 32) 21.50 -> 17.89 ms, the uneven batch 6.70 -> 4.71,
+// one 256 x 256 frame (L = 4) 37.4 -> 22.7 us.
+template <int L>
+__device__ __forceinline__ bool tone_omega(const float (&v)[L], float cw, float sw, float& omega) {
+    constexpr int m = L / 2;
+    constexpr int o = L - m;
+    constexpr bool odd = (L & 1) != 0;
+    constexpr float kSqrt2 = 1.41421356237309515f;
+    constexpr float kmax = 0.5f * (float)(L - 1);
+    // e^{j w} (odd L) or e^{j w/2} (even L, cos(w/2) >= 0), normalised in FP64
+    float fr = cw, fi = sw;
+    if (!odd) {
+        fr = fsqrt(fmaxf(0.5f * (1.f + cw), 0.f));
+        fi = fr > 1e-3f ? 0.5f * sw * frcp(fr) : 1.f;
+        if (!(fr > 1e-3f)) fr = 0.f;
+    }
+    double br = (double)fr, bi = (double)fi;
+    const double nm = fma(-0.5, fma(br, br, bi * bi), 1.5);     // 1/|b| for |b|^2 = 1 + O(1e-6)
+    br *= nm;
+    bi *= nm;
+    double Er = br, Ei = bi;                                    // e^{j w}
+    if (!odd) {
+        Er = fma(br, br, -bi * bi);
+        Ei = 2.0 * br * bi;
+    }
+    float x[m], y[m];
+    {
+        double cr = br, ci = bi;
+#pragma unroll
+        for (int i = m - 1; i >= 0; --i) {
+            const double p = (double)v[i], q = (double)v[o + i];
+            x[i] = (float)fma(p, cr, -q * ci);
+            y[i] = (float)-fma(p, ci, q * cr);
+            if (i > 0) {
+                const double t = fma(cr, Er, -ci * Ei);
+                ci = fma(cr, Ei, ci * Er);
+                cr = t;
+            }
+        }
+    }
+    auto kk = [](int i) { return kmax - (float)i; };
+    float s0 = 0.f, s1 = 0.f, s2 = 0.f;
+#pragma unroll
+    for (int i = 0; i < m; ++i) {
+        s0 += x[i];
+        s1 = fmaf(kk(i), y[i], s1);
+        s2 = fmaf(kk(i) * kk(i), x[i], s2);
+    }
+    if (odd) s0 = fmaf(v[m], 1.f / kSqrt2, s0);
+    const float a = s1 * frcp(s2);                              // -h_1 / h_2
+    if (!(s0 * s2 > 0.f && fabsf(a) <= 0.25f)) return false;
+    // x and y at w + a
+    {
+        const float al = odd ? a : 0.5f * a, a2 = al * al;
+        const float c1 = fmaf(a2, fmaf(a2, fmaf(a2, -1.f / 720.f, 1.f / 24.f), -0.5f), 1.f);
+        const float d1 = al * fmaf(a2, fmaf(a2, 1.f / 120.f, -1.f / 6.f), 1.f);
+        const float c2 = odd ? c1 : fmaf(c1, c1, -d1 * d1), d2 = odd ? d1 : 2.f * c1 * d1;
+        float cr = c1, ci = d1;
+#pragma unroll
+        for (int i = m - 1; i >= 0; --i) {
+            const float xn = fmaf(x[i], cr, y[i] * ci);
+            y[i] = fmaf(y[i], cr, -x[i] * ci);
+            x[i] = xn;
+            if (i > 0) {
+                const float t = fmaf(cr, c2, -ci * d2);
+                ci = fmaf(cr, d2, ci * c2);
+                cr = t;
+            }
+        }
+    }
+    float h0 = 0.f, h1 = 0.f, h2 = 0.f, h3 = 0.f, h4 = 0.f, h5 = 0.f;
+#pragma unroll
+    for (int i = 0; i < m; ++i) {
+        const float k = kk(i), k2 = k * k, k3 = k2 * k;
+        h0 += x[i];
+        h1 = fmaf(k, y[i], h1);
+        h2 = fmaf(-k2, x[i], h2);
+        h3 = fmaf(-k3, y[i], h3);
+        h4 = fmaf(k2 * k2, x[i], h4);
+        h5 = fmaf(k3 * k2, y[i], h5);
+    }
+    if (odd) h0 = fmaf(v[m], 1.f / kSqrt2, h0);
+    // all moments lack the factor sqrt2 (and g's sign, which the ratios drop)
+    const float sg = h0 < 0.f ? -1.f : 1.f;
+    const float dl = fmaf(-kSqrt2, fabsf(h0), sqrtf((float)L)) * (sg / kSqrt2);
+    const float ih2 = frcp(h2);
+    float T = -2.f * dl * ih2;
+    T = -2.f * fmaf(-h4 * (1.f / 24.f), T * T, dl) * ih2;
+    const float q = fmaf(fmaf(h5 * (-1.f / 120.f), T, h3 * (1.f / 6.f)), T, -h1);
+    const float iD = frcp(fmaf(-h4 * (1.f / 6.f), T, h2));
+    float xx = q * iD;
+    xx = fmaf(-0.5f * h3 * xx, xx, q) * iD;
+    if (!(fmaf(-2.f * h0, h0, (float)L) <= tone_s2(L) * (float)L && fabsf(xx) <= 3e-4f && kmax * kmax * fabsf(T) <= 0.2f))
+        return false;
+    constexpr float kPi = 3.14159265358979324f;
+    const float w = atan2f((float)Ei, (float)Er) + (a + xx);
+    omega = w > kPi ? w - 2.f * kPi : (w < -kPi ? w + 2.f * kPi : w);
+    return true;
 }
 
 // g(w) = e^{-j w (L-1)/2} B(e^{j w}) and its first two derivatives, where
@@ -971,11 +1090,8 @@ __device__ __forceinline__ void spectral_g(const float (&v)[L], float hc, float 
 // slowest lane 2.9 -> 1.0, FP64 1.7 -> 1.0, against the lag-1 direction at a
 // radius fitted to lambda_1 and K).  Any start is safe: the certificate
 // judges the root found.
-// `dep` receives L - g(w)^2 = L sin^2 of the angle between v and the steering
-// vector of the peak w: what tone_pair judges the window by.
 template <int L>
-__device__ __forceinline__ void pair_start(const float (&v)[L], float cw, float sw, double& zr, double& zi,
-                                           float& dep) {
+__device__ __forceinline__ void pair_start(const float (&v)[L], float cw, float sw, double& zr, double& zi) {
     // e^{j w/2} from e^{j w} (cos(w/2) >= 0)
     float hc = fsqrt(fmaxf(0.5f * (1.f + cw), 0.f));
     float hs = hc > 1e-3f ? 0.5f * sw * frcp(hc) : 1.f;
@@ -992,7 +1108,7 @@ __device__ __forceinline__ void pair_start(const float (&v)[L], float cw, float 
     const float nc = hc * rc - hs * rs, ns = hs * rc + hc * rs;
     spectral_g<L>(v, nc, ns, g, g1, g2);
     const float hh = fmaf(g1, g1, g * g2);
-    dep = fmaxf((float)L - g * g, 0.f);
+    const float dep = fmaxf((float)L - g * g, 0.f);
     float t = hh < 0.f ? fsqrt(dep * frcp(-hh)) : 0.01f;
     t = fminf(0.1f, fmaxf(1e-4f, finitef(t) ? t : 0.01f));
     const float r0 = __expf(-t);
@@ -1473,46 +1589,37 @@ template <int L>
 __device__ __forceinline__ void window_omega_v(const float (&v)[L], const RootTemplate& tmpl, bool full_roots,
                                                float wprev, float& omega, unsigned& flag, LaneStats& ls) {
     constexpr int n = 2 * L - 2;
-    float ur[L], ui[L];
-    signal_vector<L>(v, ur, ui);
     // frequency guess from the lag-1 coefficient c_1, or, with the temporal
     // warm start, the previous frame's frequency at this pixel
     float sw0, cw0;
-    if (finitef(wprev)) {
-        __sincosf(wprev, &sw0, &cw0);
-    } else {
-        float c1r, c1i;
-        lag1_coeff<L>(ur, ui, c1r, c1i);
-        guess_direction(c1r, c1i, cw0, sw0);
-    }
+    if (finitef(wprev)) __sincosf(wprev, &sw0, &cw0);
+    else guess_direction<L>(v, cw0, sw0);
 
     // ---- certified pair ---------------------------------------------------
-    // FP64 Newton (with the mate divided out) for the signal root from the
-    // guess w0; when its pair is certified as the pair nearest the unit
-    // circle it is the pair the selection rule picks from all roots, and its
-    // sum gives omega exactly as below.  Otherwise every root is found.
-    double zr0 = 0.0, zi0 = 0.0;
-    bool root = false;
+    // A window close to one tone in closed form.  Otherwise FP64 Newton (with
+    // the mate divided out) for the signal root from the guess w0; when its
+    // pair is certified as the pair nearest the unit circle it is the pair the
+    // selection rule picks from all roots, and its sum gives omega exactly as
+    // below.  Otherwise every root is found.
     if (!full_roots) {
-        float dep;
-        pair_start<L>(v, cw0, sw0, zr0, zi0, dep);
-        pair_newton32<L>(ur, ui, zr0, zi0, kCertIters32, &ls.pair_its32);
-        root = pair_newton<L>(ur, ui, zr0, zi0, kCertIters, &ls.pair_its);
-        if (root && tone_pair<L>(zr0, zi0, dep)) {
-            // z + 1/conj(z) = z (1 + 1/|z|^2): the pair's sum has z's own angle
-            omega = atan2f((float)zi0, (float)zr0);
+        ls.pair_its32 += 1;
+        ls.pair_its += 1;
+        if (tone_omega<L>(v, cw0, sw0, omega)) {
             ls.accepted += 1;
             return;
         }
     }
-
+    float ur[L], ui[L];
+    signal_vector<L>(v, ur, ui);
     // ---- polynomial coefficients (Eq. 12-14) -----------------------------
     float ar[n + 1], ai[n + 1];
     poly_coeffs<L>(ur, ui, ar, ai);
     bool cert = false;
-    if (root) {
-        double rr = 0.0, ri = 0.0;
-        cert = certified_root<L>(ar, ai, zr0, zi0, rr, ri);
+    if (!full_roots) {
+        double zr0, zi0, rr = 0.0, ri = 0.0;
+        pair_start<L>(v, cw0, sw0, zr0, zi0);
+        pair_newton32<L>(ur, ui, zr0, zi0, kCertIters32, &ls.pair_its32);
+        cert = pair_newton<L>(ur, ui, zr0, zi0, kCertIters, &ls.pair_its) && certified_root<L>(ar, ai, zr0, zi0, rr, ri);
         if (cert) omega = atan2f((float)ri, (float)rr);
     }
     ls.accepted += cert ? 1 : 0;

@@ -1,4 +1,4 @@
-"""The single-tone shortcut of the pair certificate (tone_pair in bm_window.h): its
+"""The single-tone shortcut of the pair certificate (tone_omega in bm_window.h): its
 constants against the bound they come from, its claim on polynomials built at the
 bound, and the kernels near it against finding every root."""
 import os
