@@ -60,7 +60,7 @@ struct RmJob {
     int len;
     int nlines;
     int N;                 // window length
-    int bpl;               // window blocks per line
+    int bpl;               // window blocks per line (RM_BLOCK: tiles per row of tiles)
     int flag_shift;        // 0 for x, 4 for y
     int flag_or;           // 1: OR into existing flags, 0: overwrite
     int kind;              // RmKind
@@ -82,7 +82,11 @@ struct RmBatch {
     int total;             // prefix[njobs]
     int jacobi;            // 1: cyclic Jacobi eigen-split instead of the tridiagonal solver
     int full_roots;        // 1: always find every root (no certified-pair shortcut)
-    int block_windows;     // 1: every job is RM_BLOCK (256-lane blocks); 0: every job is RM_LINE
+    int block_windows;     // 1: every job is RM_BLOCK (items are tiles); 0: every job is RM_LINE
+    int both_dirs;         // RM_BLOCK: 1 when some job has both directions
+    int phases;            // RM_BLOCK: 1 when some job has a phase map
+    uint8_t* left;         // RM_BLOCK above 8 x 8: one byte per work item, set where windows are left
+                           // to the second kernel (workspace)
     int warm;              // 1: some job has a previous-frame map (line windows: the warm-start kernels)
     unsigned long long* stats;  // kStatSlots x kStatFields counters, or nullptr
     RootTemplate tmpl;
@@ -198,17 +202,18 @@ struct TrBatch {
 // threads; `grid` is the number of blocks of the grid-stride loop (<= 0: one
 // block per work item).
 hipError_t launch_rootmusic(int L, const RmBatch& b, int block, int grid, hipStream_t s);
-// Lanes per block of the block-window kernels: 256, or 128 above 8 x 8.
-constexpr int block_window_lanes(int L) { return L <= kMaxL ? 256 : 128; }
+// Block windows: pixels per side of the tile that one block (256 lanes, one work item) owns.
+constexpr int kBlockTile = 16;
+inline size_t block_tiles(int W, int H) {
+    return (size_t)((W + kBlockTile - 1) / kBlockTile) * (size_t)((H + kBlockTile - 1) / kBlockTile);
+}
 // Block windows above 8 x 8 (odd sizes to kMaxBlockL), in their own translation unit.
-hipError_t launch_big_block_window(int L, const RmBatch& b, int grid, hipStream_t s);
-hipError_t launch_big_block_window_15_17(int L, const RmBatch& b, int grid, hipStream_t s);
+hipError_t launch_big_block_window(int L, const RmBatch& b, hipStream_t s);
+hipError_t launch_big_block_window_15_17(int L, const RmBatch& b, hipStream_t s);
 // The same launch with the cyclic Jacobi eigen-split (L <= 8).
 hipError_t launch_rootmusic_jacobi(int L, const RmBatch& b, int block, int grid, hipStream_t s);
-// Output pixels per work item of a line: the line-window root-MUSIC kernel
-// (line_kernel) covers two starts per lane, the block-window and surrogate
-// kernels one.
-int rootmusic_windows_per_block(int L, int block, bool line_kernel);
+// Output pixels per work item of the line-window and surrogate kernels.
+int rootmusic_windows_per_block(int L, int block);
 // Plain root-MUSIC on the *count windows of `list` ({job, line << 16 | pixel};
 // lines and pixels are below 65536 because frame sides are), grid-stride over
 // `grid` blocks of kGatherBlock lanes.

@@ -1,7 +1,7 @@
 // Launchers of the root-MUSIC kernels with the cyclic Jacobi eigen-split
 // (BM_OPT_JACOBI) for line windows and block windows up to 8 x 8: their own
 // translation unit, so that they compile alongside the default ones.
-#include "bm_rootmusic_kernels.h"
+#include "bm_block_kernels.h"
 
 namespace bm {
 

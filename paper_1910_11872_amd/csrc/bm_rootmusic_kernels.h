@@ -144,103 +144,6 @@ __device__ __forceinline__ void rootmusic_block(const RmJob& J, int line, int p0
 }
 
 
-// One block of pixels p0 .. p0+BLOCK-L of line `line` in block mode (the
-// paper's L x L moving window, Sec. 3): the rows line-h .. line-h+L-1 of the
-// window columns p0-h .. are staged in LDS; each lane sums its block's real
-// symmetric T straight from the block's rows (omega_x) and from its columns
-// (omega_y) as snapshots, s_k[i] = G[k][t+i] or G[i][t+k] (Eq. 4).
-// With the snapshots read in increasing x (or y), omega = +arg of the
-// selected root in both directions -- the paper's -arg(z_x) for its
-// E{Gamma^H Gamma} form.  With both frequencies, the block phase (Eq. 15's
-// alpha, block coordinates measured from the pixel) is
-// arg sum_{i,j} G[i][j] e^{-j(omega_x (j-h) + omega_y (i-h))}.
-template <int L, int BLOCK, bool JACOBI>
-__device__ __forceinline__ void rootmusic_block2d(const RmJob& J, int line, int p0, float2 (*sR)[BLOCK + L],
-                                                  const RootTemplate& tmpl, bool full_roots, LaneStats& ls) {
-    constexpr int WPB = BLOCK - (L - 1);
-    constexpr int h = L / 2;
-    const int t = threadIdx.x;
-    const int len = J.len, nl = J.nlines;
-    const int c0 = p0 - h, r0 = line - h;
-#pragma unroll
-    for (int i = 0; i < L; ++i) {
-        const int r = r0 + i;
-        const bool rin = r >= 0 && r < nl;
-        const float2* g = J.gamma + (int64_t)(rin ? r : 0) * J.gamma_ls;
-        for (int c = t; c < BLOCK + L - 1; c += BLOCK) {
-            const int q = c0 + c;
-            sR[i][c] = (rin && q >= 0 && q < len) ? g[q] : make_float2(0.f, 0.f);
-        }
-    }
-    __syncthreads();
-    const int p = p0 + t;
-    const bool inside_line = (t < WPB) && (p < len);
-    const bool valid = inside_line && (c0 + t >= 0) && (c0 + t + L <= len) && (r0 >= 0) && (r0 + L <= nl);
-    float wx = __builtin_nanf(""), wy = __builtin_nanf(""), ph = __builtin_nanf("");
-    unsigned fx = 0, fy = 0;
-    if (valid) {
-        if (J.bdirs & BM_DIR_X) {
-            Sym<L> T;
-            float c1r, c1i, hc, hs;
-            T_from_snapshots<L>(L, [&](int k, int i) { return sR[k][t + i]; }, T, c1r, c1i);
-            half_angle_of(c1r, c1i, hc, hs);
-            if (trace_normalise<L>(T))
-                window_omega_Ts<L, JACOBI>(T, hc, hs, tmpl, full_roots, __builtin_nanf(""), wx, fx, ls);
-            else fx |= BM_FLAG_UNDEFINED;
-        }
-        if (J.bdirs & BM_DIR_Y) {
-            Sym<L> T;
-            float c1r, c1i, hc, hs;
-            T_from_snapshots<L>(L, [&](int k, int i) { return sR[i][t + k]; }, T, c1r, c1i);
-            half_angle_of(c1r, c1i, hc, hs);
-            if (trace_normalise<L>(T))
-                window_omega_Ts<L, JACOBI>(T, hc, hs, tmpl, full_roots, __builtin_nanf(""), wy, fy, ls);
-            else fy |= BM_FLAG_UNDEFINED;
-        }
-        if (J.phase && finitef(wx) && finitef(wy)) {
-            // the hardware sine and cosine: arguments stay within |w| (L/2) <= 4 pi,
-            // where their error (~1e-6) is far below the phase tolerance, and the
-            // library's large-argument reduction would hold registers the whole
-            // kernel pays for (two waves per SIMD instead of three or four)
-            float exr[L], exi[L];
-#pragma unroll
-            for (int j = 0; j < L; ++j) {
-                float sn, cs;
-                __sincosf(wx * (float)(j - h), &sn, &cs);
-                exr[j] = cs;
-                exi[j] = -sn;
-            }
-            float ar = 0.f, ai = 0.f;
-#pragma unroll
-            for (int i = 0; i < L; ++i) {
-                float rr = 0.f, ri = 0.f;     // sum_j G[i][j] e^{-j wx (j-h)}
-#pragma unroll
-                for (int j = 0; j < L; ++j) {
-                    const float2 v = sR[i][t + j];
-                    rr = fmaf(v.x, exr[j], fmaf(-v.y, exi[j], rr));
-                    ri = fmaf(v.x, exi[j], fmaf(v.y, exr[j], ri));
-                }
-                float sn, cs;
-                __sincosf(wy * (float)(i - h), &sn, &cs);   // times e^{-j wy (i-h)}
-                ar = fmaf(rr, cs, fmaf(ri, sn, ar));
-                ai = fmaf(ri, cs, fmaf(-rr, sn, ai));
-            }
-            ph = atan2f(ai, ar);
-        }
-    } else {
-        fx = fy = BM_FLAG_UNDEFINED;
-    }
-    if (inside_line) {
-        const int64_t o = (int64_t)p * J.out_es + (int64_t)line * J.out_ls;
-        if (J.bdirs & BM_DIR_X) J.out[o] = wx;
-        if (J.bdirs & BM_DIR_Y) J.out_y[o] = wy;
-        if (J.phase) J.phase[o] = ph;
-        if (J.flags)
-            J.flags[(int64_t)p * J.flag_es + (int64_t)line * J.flag_ls] =
-                (uint8_t)(((J.bdirs & BM_DIR_X) ? fx : 0u) | (((J.bdirs & BM_DIR_Y) ? fy : 0u) << 4));
-    }
-}
-
 template <int BLOCK>
 __device__ __forceinline__ void flush_stats(const LaneStats& ls, unsigned long long* stats) {
     unsigned long long a[kStatFields] = {(unsigned long long)ls.counted, (unsigned long long)ls.eig_its,
@@ -269,26 +172,19 @@ __device__ __forceinline__ void flush_stats(const LaneStats& ls, unsigned long l
 // Without the statistics counters the L <= 6 line kernels fit five waves per
 // SIMD (96 VGPRs, a few spilled), 1.3% faster on L = 6 than the four that 119
 // VGPRs allow, and the L = 7, 8 ones four (128 VGPRs; L = 8 spills seven and
-// runs 3% faster than at the three waves of its 151).  The block-window
-// kernels run four too (L = 7: 143 -> 128 VGPRs with no spill, 11% faster;
-// L = 8: 160 -> 128 with 14 spilled, 8% faster).
-// Block windows above 8 x 8 (odd sizes to 17 x 17) run 128 lanes per block at
-// one wave per SIMD: the per-lane T, the degree 2L-2 polynomial and the FP64
-// certificate need up to 512 VGPRs.
+// runs 3% faster than at the three waves of its 151).
 // WARM: line windows may read a previous-frame map (the other build folds the
 // warm-start branch away: four fewer spilled registers at L = 8).
 // LOOP = false (line windows): one block per work item (grid = total), no
 // grid-stride loop; the loop keeps values live across items that cost the
 // L = 6 and 8 line kernels 40-50 spilled registers.
-template <int L, int BLOCK, bool STATS, bool JACOBI, bool BLOCKWIN, bool WARM = false, bool LOOP = true>
+template <int L, int BLOCK, bool STATS, bool JACOBI, bool WARM = false, bool LOOP = true>
 __global__ __launch_bounds__(BLOCK)
-__attribute__((amdgpu_waves_per_eu((!STATS && L <= kMaxL) ? (BLOCKWIN ? 4 : (L <= 6 ? 5 : 4)) : 1)))
+__attribute__((amdgpu_waves_per_eu(STATS ? 1 : (L <= 6 ? 5 : 4))))
 void rootmusic_kernel(RmBatch B) {
-    // line windows: staged signal + lag sums; block windows: the block's staged rows
-    constexpr int ROW = BLOCKWIN ? BLOCK + L : LineSpan<L, BLOCK>::row;
-    constexpr int WPB = BLOCKWIN ? BLOCK - (L - 1) : LineSpan<L, BLOCK>::wpb;
-    __shared__ float2 sg[BLOCKWIN ? 1 : 4 * LineSpan<L, BLOCK>::quarter];
-    __shared__ __align__(16) float2 sS[L][ROW];
+    // staged signal and lag sums
+    __shared__ float2 sg[4 * LineSpan<L, BLOCK>::quarter];
+    __shared__ __align__(16) float2 sS[L][LineSpan<L, BLOCK>::row];
     LaneStats ls;
     // LOOP = false: exactly one item, blockIdx.x (a trip count of one the compiler sees)
     const int wend = LOOP ? B.total : (int)blockIdx.x + 1;
@@ -299,12 +195,8 @@ void rootmusic_kernel(RmBatch B) {
         const int local = w - B.prefix[j];
         const int line = local / J.bpl;
         const int bx = local - line * J.bpl;
-        // line and block windows are separate instantiations, so that neither
-        // pays the other's registers
-        if constexpr (BLOCKWIN)
-            rootmusic_block2d<L, BLOCK, JACOBI>(J, line, bx * WPB, sS, B.tmpl, B.full_roots != 0, ls);
-        else
-            rootmusic_block<L, BLOCK, JACOBI, WARM>(J, line, bx * WPB, sg, sS, B.tmpl, B.full_roots != 0, ls);
+        rootmusic_block<L, BLOCK, JACOBI, WARM>(J, line, bx * LineSpan<L, BLOCK>::wpb, sg, sS, B.tmpl,
+                                                B.full_roots != 0, ls);
         __syncthreads();
     }
     if (STATS) flush_stats<BLOCK>(ls, B.stats);
@@ -356,12 +248,12 @@ __global__ __launch_bounds__(kGatherBlock) void rootmusic_gather_kernel(RmBatch 
 template <int L, int BLOCK, bool JACOBI, bool WARM>
 hipError_t launch_LBJW(const RmBatch& b, int grid, hipStream_t s) {
     if (b.stats)
-        hipLaunchKernelGGL((rootmusic_kernel<L, BLOCK, true, JACOBI, false, WARM>), dim3(grid), dim3(BLOCK), 0, s, b);
+        hipLaunchKernelGGL((rootmusic_kernel<L, BLOCK, true, JACOBI, WARM>), dim3(grid), dim3(BLOCK), 0, s, b);
     else if (grid < b.total)
-        hipLaunchKernelGGL((rootmusic_kernel<L, BLOCK, false, JACOBI, false, WARM>), dim3(grid), dim3(BLOCK), 0, s,
+        hipLaunchKernelGGL((rootmusic_kernel<L, BLOCK, false, JACOBI, WARM>), dim3(grid), dim3(BLOCK), 0, s,
                            b);
     else
-        hipLaunchKernelGGL((rootmusic_kernel<L, BLOCK, false, JACOBI, false, WARM, false>), dim3(b.total),
+        hipLaunchKernelGGL((rootmusic_kernel<L, BLOCK, false, JACOBI, WARM, false>), dim3(b.total),
                            dim3(BLOCK), 0, s, b);
     return hipGetLastError();
 }
@@ -369,47 +261,6 @@ hipError_t launch_LBJW(const RmBatch& b, int grid, hipStream_t s) {
 template <int L, int BLOCK, bool JACOBI>
 hipError_t launch_LBJ(const RmBatch& b, int grid, hipStream_t s) {
     return b.warm ? launch_LBJW<L, BLOCK, JACOBI, true>(b, grid, s) : launch_LBJW<L, BLOCK, JACOBI, false>(b, grid, s);
-}
-
-// Block windows: 256 lanes per block (128 above 8 x 8).
-template <int L, bool JACOBI>
-hipError_t launch_block_LJ(const RmBatch& b, int grid, hipStream_t s) {
-    constexpr int BL = block_window_lanes(L);
-    if (b.stats)
-        hipLaunchKernelGGL((rootmusic_kernel<L, BL, true, JACOBI, true>), dim3(grid), dim3(BL), 0, s, b);
-    else
-        hipLaunchKernelGGL((rootmusic_kernel<L, BL, false, JACOBI, true>), dim3(grid), dim3(BL), 0, s, b);
-    return hipGetLastError();
-}
-
-// Block windows above 8 x 8: the tridiagonal solver only.
-template <int L>
-hipError_t launch_big_block(const RmBatch& b, int grid, hipStream_t s) {
-    if (!b.block_windows) return hipErrorInvalidValue;
-    return launch_block_LJ<L, false>(b, grid, s);
-}
-
-// Line and block windows up to 8 x 8 of one eigen solver (JACOBI or the
-// default route), one translation unit each.
-template <int L, bool JACOBI>
-hipError_t launch_LJ(const RmBatch& b, int block, int grid, hipStream_t s) {
-    if (b.block_windows) return launch_block_LJ<L, JACOBI>(b, grid, s);
-    if (block == 128) return launch_LBJ<L, 128, JACOBI>(b, grid, s);
-    return launch_LBJ<L, 256, JACOBI>(b, grid, s);
-}
-
-template <bool JACOBI>
-hipError_t launch_rootmusic_J(int L, const RmBatch& b, int block, int grid, hipStream_t s) {
-    switch (L) {
-        case 2: return launch_LJ<2, JACOBI>(b, block, grid, s);
-        case 3: return launch_LJ<3, JACOBI>(b, block, grid, s);
-        case 4: return launch_LJ<4, JACOBI>(b, block, grid, s);
-        case 5: return launch_LJ<5, JACOBI>(b, block, grid, s);
-        case 6: return launch_LJ<6, JACOBI>(b, block, grid, s);
-        case 7: return launch_LJ<7, JACOBI>(b, block, grid, s);
-        case 8: return launch_LJ<8, JACOBI>(b, block, grid, s);
-        default: return hipErrorInvalidValue;
-    }
 }
 
 template <int L, bool JACOBI>

@@ -409,7 +409,9 @@ bm_status validate_frame(bosmusic_s* h, const bosmusic_frame& f, int idx) {
 
 size_t frame_ws_bytes(const bosmusic_frame& f) {
     const size_t px = (size_t)f.width * (size_t)f.height;
-    if (f.dirs & BM_BLOCK) return f.dtype != BM_C32 ? align_up(px * sizeof(float2), 256) : 0;
+    if (f.dirs & BM_BLOCK)
+        return (f.dtype != BM_C32 ? align_up(px * sizeof(float2), 256) : 0) +
+               (f.L > bm::kMaxL ? align_up(bm::block_tiles(f.width, f.height), 256) : 0);
     size_t b = 0;
     if ((f.dirs & BM_DIR_X) && f.dtype != BM_C32) b += align_up(px * sizeof(float2), 256);
     if (f.dirs & BM_DIR_Y) {
@@ -428,6 +430,7 @@ struct RmSet {
     bool block_win = false;         // block-window jobs (their own kernel instantiation)
     std::vector<bm::RmJob> jobs;
     std::vector<int> prefix;
+    uint8_t* left = nullptr;        // block windows above 8 x 8: marks of the tiles (workspace)
     size_t jobs_off = 0, prefix_off = 0;
     bm::RmBatch batch{};
     Tune tune;
@@ -614,7 +617,6 @@ bm_status plan_group(bosmusic_s* h, const bosmusic_frame* frames, int i0, int i1
             add_rm(f.L, any_flags && (f.dirs & BM_DIR_X), j);
         }
     }
-    if (cur > h->ws_bytes) return fail(h, BM_E_INVALID_ARG, "group exceeds the workspace");
     gp.tr_prefix.assign(1, 0);
     for (auto& t : gp.tr)
         gp.tr_prefix.push_back(gp.tr_prefix.back() + t.tiles_x * ((t.rows + bm::tr_tile(t) - 1) / bm::tr_tile(t)));
@@ -639,19 +641,32 @@ bm_status plan_group(bosmusic_s* h, const bosmusic_frame* frames, int i0, int i1
         RmSet s = kv.second;
         int nmax = 0;
         for (auto& j : s.jobs) nmax = std::max(nmax, j.N);
-        // the surrogate and block-window kernels run 256 lanes (128 for block windows
-        // above 8 x 8), one block per item; plain line windows take the tuned tile
+        // the surrogate and block-window kernels run 256 lanes, one block per item;
+        // plain line windows take the tuned tile
         if (mode == BM_SURROGATE || s.block_win) s.tune = Tune{};
         else s.tune = h->tune[s.L][nmax];
-        if (s.block_win) s.tune.block = bm::block_window_lanes(s.L);
-        const int wpb = bm::rootmusic_windows_per_block(s.L, s.tune.block, !s.block_win);
         s.prefix.assign(1, 0);
-        for (auto& j : s.jobs) {
-            j.bpl = (j.len + wpb - 1) / wpb;
-            s.prefix.push_back(s.prefix.back() + j.bpl * j.nlines);
+        if (s.block_win) {
+            // one item per tile of kBlockTile x kBlockTile pixels
+            constexpr int T = bm::kBlockTile;
+            for (auto& j : s.jobs) {
+                j.bpl = (j.len + T - 1) / T;
+                s.prefix.push_back(s.prefix.back() + j.bpl * ((j.nlines + T - 1) / T));
+            }
+            if (s.L > bm::kMaxL) {
+                s.left = (uint8_t*)(h->ws + cur);
+                cur += align_up((size_t)s.prefix.back(), 256);
+            }
+        } else {
+            const int wpb = bm::rootmusic_windows_per_block(s.L, s.tune.block);
+            for (auto& j : s.jobs) {
+                j.bpl = (j.len + wpb - 1) / wpb;
+                s.prefix.push_back(s.prefix.back() + j.bpl * j.nlines);
+            }
         }
         gp.rm.push_back(s);
     }
+    if (cur > h->ws_bytes) return fail(h, BM_E_INVALID_ARG, "group exceeds the workspace");
     gp.mode = mode;
     gp.blob.clear();
     gp.tr_off = append(gp.blob, gp.tr);
@@ -692,7 +707,13 @@ void bind_group(bosmusic_s* h, GroupPlan& gp, const char* dev) {
         s.batch.full_roots = (h->options & BM_OPT_FULL_ROOTS) ? 1 : 0;
         s.batch.block_windows = s.block_win ? 1 : 0;
         s.batch.warm = 0;
-        for (auto& jb : s.jobs) s.batch.warm |= jb.prev ? 1 : 0;
+        s.batch.left = s.left;
+        s.batch.both_dirs = s.batch.phases = 0;
+        for (auto& jb : s.jobs) {
+            s.batch.warm |= jb.prev ? 1 : 0;
+            s.batch.both_dirs |= jb.bdirs == (int)(BM_DIR_X | BM_DIR_Y) ? 1 : 0;
+            s.batch.phases |= jb.phase ? 1 : 0;
+        }
         s.batch.stats = (h->options & BM_OPT_STATS) ? h->stats : nullptr;
         s.batch.tmpl = h->tmpl[s.L];
     }
@@ -1774,7 +1795,7 @@ bm_status bosmusic_autotune(bosmusic_t h, int32_t L, int32_t N, int32_t width, i
             j.len = width;
             j.nlines = lines;
             j.N = N;
-            const int wpb = bm::rootmusic_windows_per_block(L, blocks[bi], true);
+            const int wpb = bm::rootmusic_windows_per_block(L, blocks[bi]);
             j.bpl = (width + wpb - 1) / wpb;
             int prefix[2] = {0, j.bpl * lines};
             // the previous candidate's launches read the table: wait before rewriting it

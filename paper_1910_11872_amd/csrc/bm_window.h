@@ -1318,13 +1318,20 @@ __device__ __forceinline__ void T_from_snapshots(int K, F snap, Sym<L>& T, float
         for (int j = i; j < L; ++j) T.a[i][j] = 0.f;
     c1r = 0.f;
     c1i = 0.f;
-    // one snapshot at a time: unrolled, the loads of all snapshots would be
-    // hoisted and held in registers
+    // one snapshot at a time (unrolled, the loads of all snapshots would be
+    // hoisted and held in registers), the next one's loads in flight meanwhile
+    float2 next[L];
+#pragma unroll
+    for (int i = 0; i < L; ++i) next[i] = snap(0, i);
 #pragma unroll 1
     for (int k = 0; k < K; ++k) {
         float2 v[L];
 #pragma unroll
-        for (int i = 0; i < L; ++i) v[i] = snap(k, i);
+        for (int i = 0; i < L; ++i) v[i] = next[i];
+        if (k + 1 < K) {
+#pragma unroll
+            for (int i = 0; i < L; ++i) next[i] = snap(k + 1, i);
+        }
         // lag-1 sum: sum_i conj(s[i]) s[i+1]
 #pragma unroll
         for (int i = 0; i + 1 < L; ++i) {
