@@ -96,21 +96,25 @@ __device__ __forceinline__ void rootmusic_block(const RmJob& J, int line, int p0
 
     // window of pixel p0+s starts at base+s
     const int base = p0 - half;
-    // ---- lag sums S_d(base + s), s < SPAN, d < L -----------------------------
+    // ---- lag sums S_d(base + s), s < need, d < L -----------------------------
+    // (a line's last block holds fewer windows: 1024-sample lines end in one of 12-16,
+    // which cost 5% of 100 x 1024^2 when it staged and summed a whole block's starts)
+    const int need = min(SPAN, len - p0 + L - 1);
     if constexpr (LineSpan<L, BLOCK>::quad) {
-        for (int i = t; i < SPAN + N; i += BLOCK) {        // one sample more for the odd-L dummy lag
+        for (int i = t; i < min(need + 3, SPAN) + N; i += BLOCK) {   // whole quads, and one for the odd-L dummy lag
             const int q = base + i;
             sg[sg_slot(i, LineSpan<L, BLOCK>::quarter)] = (q >= 0 && q < len) ? g[q] : make_float2(0.f, 0.f);
         }
         __syncthreads();
-        lag_sums_quad<L, LineSpan<L, BLOCK>::row, LineSpan<L, BLOCK>::quarter>(sg, t, K, sS);
+        if (2 * (t & ~1) < need)
+            lag_sums_quad<L, LineSpan<L, BLOCK>::row, LineSpan<L, BLOCK>::quarter>(sg, t, K, sS);
     } else {
-        for (int i = t; i < SPAN + N - 1; i += BLOCK) {
+        for (int i = t; i < need + N; i += BLOCK) {
             const int q = base + i;
             sg[i] = (q >= 0 && q < len) ? g[q] : make_float2(0.f, 0.f);
         }
         __syncthreads();
-        lag_sums_pair<L, LineSpan<L, BLOCK>::row>(sg, kLineSpan * t, K, sS);
+        if (kLineSpan * t < need) lag_sums_pair<L, LineSpan<L, BLOCK>::row>(sg, kLineSpan * t, K, sS);
     }
     __syncthreads();
 

@@ -275,7 +275,7 @@ void surrogate_kernel(SurBatch S) {
     }
     __syncthreads();
     // ---- lag sums (the MLP scratch is dead: every wave passed the barrier) ---
-    lag_sums_pair<L, ROW>(sg, 2 * t, K, sS);
+    if (2 * t < min(SPAN, len - p0 + L - 1)) lag_sums_pair<L, ROW>(sg, 2 * t, K, sS);
     __syncthreads();
 
     LaneStats ls;
