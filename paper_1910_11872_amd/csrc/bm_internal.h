@@ -19,7 +19,6 @@ constexpr int kMaxFFT = 8192;
 constexpr int kMaxRadixPasses = 20;
 constexpr int kStatSlots = 64;   // counter slots of the statistics buffer
 constexpr int kStatFields = 9;   // counters per slot
-constexpr int kGatherBlock = 256;
 
 // Mixed-radix plan of one DFT length (radices 4, 2, 3, 5, 7, 11, 13 in pass order).
 struct FftPlan {
@@ -214,12 +213,6 @@ hipError_t launch_big_block_window_15_17(int L, const RmBatch& b, hipStream_t s)
 hipError_t launch_rootmusic_jacobi(int L, const RmBatch& b, int block, int grid, hipStream_t s);
 // Output pixels per work item of the line-window and surrogate kernels.
 int rootmusic_windows_per_block(int L, int block);
-// Plain root-MUSIC on the *count windows of `list` ({job, line << 16 | pixel};
-// lines and pixels are below 65536 because frame sides are), grid-stride over
-// `grid` blocks of kGatherBlock lanes.
-hipError_t launch_rootmusic_gather(int L, const RmBatch& b, const int2* list, const unsigned long long* count,
-                                   int grid, hipStream_t s);
-
 // Surrogate MLP 32 -> 64 -> 64 -> 2 (GELU), bfloat16 weights stored
 // transposed (out x in) for the MFMA A operand, FP32 biases.
 struct MlpWeights {
@@ -247,15 +240,13 @@ struct SurBatch {
 hipError_t launch_surrogate(int L, const SurBatch& b, hipStream_t s);
 // Y[M x 2] = MLP(X[M x 32]) with the kernel's bfloat16 arithmetic.
 hipError_t launch_mlp_forward(const MlpWeights& w, const float* X, float* Y, int M, hipStream_t s);
-hipError_t launch_fill_u64(unsigned long long* p, int n, unsigned long long v, hipStream_t s);
 
-// Surrogate training.  Lines of 128 samples drawn by counter (Philox4x32-10)
-// for ids first .. first+count-1; label windows {job = i >> 16, line = i & 0xFFFF,
-// pixel 64}; features and targets of the centre window of each line.
-hipError_t launch_gen_lines(float* lines, long long first, int count, unsigned long long seed, hipStream_t s);
-hipError_t launch_label_entries(int2* list, int count, hipStream_t s);
-hipError_t launch_train_features(const float2* gamma, int count, const float* labels, float* X, float* T,
-                                 hipStream_t s);
+// Surrogate training set: lines first .. first+count-1 of 128 samples drawn by
+// counter (Philox4x32-10), features X[count][32] of their centre windows,
+// targets T[count][2] and, when not null, labels[count]; gamma holds the windows
+// in between (32 * count complex samples).
+hipError_t launch_train_set(long long first, int count, unsigned long long seed, const RootTemplate& tmpl, int jacobi,
+                            int full_roots, float2* gamma, float* X, float* T, float* labels, hipStream_t s);
 int mlp_train_blocks(int M);
 int mlp_partial_stride();
 // Per-block gradient partials of the mean squared error over M samples (M % 64 == 0).

@@ -14,13 +14,4 @@ hipError_t launch_rootmusic(int L, const RmBatch& b, int block, int grid, hipStr
     return b.jacobi ? launch_rootmusic_jacobi(L, b, block, grid, s) : launch_rootmusic_J<false>(L, b, block, grid, s);
 }
 
-// The training labels: L = 8 only.
-hipError_t launch_rootmusic_gather(int L, const RmBatch& b, const int2* list, const unsigned long long* count, int grid,
-                                   hipStream_t s) {
-    if (grid <= 0) return hipSuccess;
-    if (L != 8) return hipErrorInvalidValue;
-    return b.jacobi ? launch_gather_LJ<8, true>(b, list, count, grid, s)
-                    : launch_gather_LJ<8, false>(b, list, count, grid, s);
-}
-
 }  // namespace bm

@@ -206,49 +206,6 @@ void rootmusic_kernel(RmBatch B) {
     if (STATS) flush_stats<BLOCK>(ls, B.stats);
 }
 
-// Plain root-MUSIC on a list of windows (job, line, pixel), one lane each,
-// with the covariance summed directly from the analytic signal.
-template <int L, bool STATS, bool JACOBI>
-__global__ __launch_bounds__(kGatherBlock) void rootmusic_gather_kernel(RmBatch B, const int2* list,
-                                                                        const unsigned long long* count) {
-    const unsigned long long cnt = *count;
-    LaneStats ls;
-    for (unsigned long long e = (unsigned long long)blockIdx.x * kGatherBlock + threadIdx.x; e < cnt;
-         e += (unsigned long long)gridDim.x * kGatherBlock) {
-        const int2 en = list[e];
-        const RmJob J = B.jobs[en.x];
-        const int line = (int)((unsigned)en.y >> 16), p = en.y & 0xFFFF;
-        const int N = J.N;
-        const int K = N - L + 1;
-        const float2* g = J.gamma + (int64_t)line * J.gamma_ls + (p - (N >> 1));
-        Cov<L> R;
-#pragma unroll
-        for (int i = 0; i < L; ++i)
-#pragma unroll
-            for (int j = i; j < L; ++j) { R.re[i][j] = 0.f; R.im[i][j] = 0.f; }
-        float2 win[L];
-#pragma unroll
-        for (int d = 0; d < L - 1; ++d) win[d + 1] = g[d];
-        for (int k = 0; k < K; ++k) {
-#pragma unroll
-            for (int d = 0; d < L - 1; ++d) win[d] = win[d + 1];
-            win[L - 1] = g[k + L - 1];
-#pragma unroll
-            for (int i = 0; i < L; ++i)
-#pragma unroll
-                for (int jj = i; jj < L; ++jj) {
-                    R.re[i][jj] = fmaf(win[i].x, win[jj].x, fmaf(win[i].y, win[jj].y, R.re[i][jj]));
-                    if (i != jj) R.im[i][jj] = fmaf(win[i].y, win[jj].x, fmaf(-win[i].x, win[jj].y, R.im[i][jj]));
-                }
-        }
-        float omega = __builtin_nanf("");
-        unsigned flag = 0;
-        window_omega<L, JACOBI>(R, B.tmpl, B.full_roots != 0, K, __builtin_nanf(""), omega, flag, ls);
-        store_omega(J, line, p, omega, flag);
-    }
-    if (STATS) flush_stats<kGatherBlock>(ls, B.stats);
-}
-
 template <int L, int BLOCK, bool JACOBI, bool WARM>
 hipError_t launch_LBJW(const RmBatch& b, int grid, hipStream_t s) {
     if (b.stats)
@@ -266,19 +223,6 @@ template <int L, int BLOCK, bool JACOBI>
 hipError_t launch_LBJ(const RmBatch& b, int grid, hipStream_t s) {
     return b.warm ? launch_LBJW<L, BLOCK, JACOBI, true>(b, grid, s) : launch_LBJW<L, BLOCK, JACOBI, false>(b, grid, s);
 }
-
-template <int L, bool JACOBI>
-hipError_t launch_gather_LJ(const RmBatch& b, const int2* list, const unsigned long long* count, int grid, hipStream_t s) {
-    if (b.stats)
-        hipLaunchKernelGGL((rootmusic_gather_kernel<L, true, JACOBI>), dim3(grid), dim3(kGatherBlock), 0, s, b, list,
-                           count);
-    else
-        hipLaunchKernelGGL((rootmusic_gather_kernel<L, false, JACOBI>), dim3(grid), dim3(kGatherBlock), 0, s, b,
-                           list, count);
-    return hipGetLastError();
-}
-
-
 
 }  // namespace
 }  // namespace bm

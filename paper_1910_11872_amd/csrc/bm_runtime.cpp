@@ -1150,94 +1150,28 @@ bm_status bosmusic_surrogate_dataset(bosmusic_t h, int64_t first_line, int64_t c
         DeviceGuard dg(h->device);
         hipStream_t st = (hipStream_t)stream;
         bm_status r;
-        constexpr int kLen = 128, kLabelL = 8, kLabelN = 32, kPerJob = 65536;
+        constexpr int kLabelL = 8, kWindow = 32;
         constexpr int64_t kChunk = (int64_t)1 << 18;
-        constexpr int kMaxJobs = (int)(kChunk / kPerJob);
         const int64_t chunk = std::min(count, kChunk);
-        size_t off = 0;
-        auto carve = [&](size_t bytes) { const size_t o = off; off = align_up(off + bytes, 256); return o; };
-        const size_t o_lines = carve((size_t)chunk * kLen * sizeof(float));
-        const size_t o_gamma = carve((size_t)chunk * kLen * sizeof(float2));
-        const size_t o_labels = carve((size_t)chunk * sizeof(float));
-        const size_t o_list = carve((size_t)chunk * sizeof(int2));
-        const size_t o_count = carve(sizeof(unsigned long long));
-        const size_t o_fj = carve(sizeof(bm::FftJob));
-        const size_t o_fp = carve(2 * sizeof(int));
-        const size_t o_rj = carve(kMaxJobs * sizeof(bm::RmJob));
-        const size_t o_rp = carve((kMaxJobs + 1) * sizeof(int));
-        if (off > h->ds_bytes) {
+        // the label windows' analytic signal of one chunk (the next chunk's kernels
+        // follow on the same stream)
+        const size_t need = (size_t)chunk * kWindow * sizeof(float2);
+        if (need > h->ds_bytes) {
             if ((r = check(h, hipStreamSynchronize(st), "sync"))) return r;
             (void)hipFree(h->ds);
             h->ds = nullptr;
             h->ds_bytes = 0;
-            if (hipMalloc(&h->ds, off) != hipSuccess) return fail(h, BM_E_NOMEM, "dataset buffers (%zu bytes)", off);
-            h->ds_bytes = off;
+            if (hipMalloc(&h->ds, need) != hipSuccess) return fail(h, BM_E_NOMEM, "dataset buffers (%zu bytes)", need);
+            h->ds_bytes = need;
         }
-        bm::FftJob fj{};
-        if ((r = make_fft_job(h, kLen, fj))) return r;
-        float* lines = (float*)(h->ds + o_lines);
-        float2* gamma = (float2*)(h->ds + o_gamma);
         for (int64_t c0 = 0; c0 < count; c0 += chunk) {
             const int n = (int)std::min(chunk, count - c0);
-            float* labels = omega ? omega + c0 : (float*)(h->ds + o_labels);
-            fj.src = lines;
-            fj.src_ls = kLen;
-            fj.dst = gamma;
-            fj.elem = BM_F32;
-            fj.nlines = n;
-            const int fprefix[2] = {0, bm::fft_items(fj)};
-            std::vector<bm::RmJob> rj;
-            std::vector<int> rp(1, 0);
-            for (int j = 0; j * kPerJob < n; ++j) {
-                bm::RmJob J{};
-                J.gamma = gamma + (int64_t)j * kPerJob * kLen;
-                J.gamma_ls = kLen;
-                J.out = labels + (int64_t)j * kPerJob;
-                J.out_es = 0;
-                J.out_ls = 1;
-                J.len = kLen;
-                J.nlines = std::min(kPerJob, n - j * kPerJob);
-                J.N = kLabelN;
-                J.bpl = 1;
-                rj.push_back(J);
-                rp.push_back(rp.back() + J.nlines);
-            }
-            // the tables are read by this chunk's kernels: finish the previous chunk first
-            if ((r = check(h, hipStreamSynchronize(st), "sync")) ||
-                (r = check(h, hipMemcpy(h->ds + o_fj, &fj, sizeof(fj), hipMemcpyHostToDevice), "tables")) ||
-                (r = check(h, hipMemcpy(h->ds + o_fp, fprefix, sizeof(fprefix), hipMemcpyHostToDevice), "tables")) ||
-                (r = check(h, hipMemcpy(h->ds + o_rj, rj.data(), rj.size() * sizeof(bm::RmJob), hipMemcpyHostToDevice),
-                           "tables")) ||
-                (r = check(h, hipMemcpy(h->ds + o_rp, rp.data(), rp.size() * sizeof(int), hipMemcpyHostToDevice),
-                           "tables")))
-                return r;
-            bm::FftBatch fb;
-            fb.jobs = (const bm::FftJob*)(h->ds + o_fj);
-            fb.prefix = (const int*)(h->ds + o_fp);
-            fb.njobs = 1;
-            fb.total = fprefix[1];
-            for (int c = 0; c <= bm::kFftClasses; ++c) fb.cls_from[c] = c <= bm::fft_class(fj) ? 0 : fb.total;
-            for (int c = 0; c < bm::kFftClasses; ++c) fb.lds[c] = bm::fft_lds_elems(fj);
-            bm::RmBatch rb{};
-            rb.jobs = (const bm::RmJob*)(h->ds + o_rj);
-            rb.prefix = (const int*)(h->ds + o_rp);
-            rb.njobs = (int)rj.size();
-            rb.total = n;
-            rb.jacobi = (h->options & BM_OPT_JACOBI) ? 1 : 0;
-            rb.full_roots = (h->options & BM_OPT_FULL_ROOTS) ? 1 : 0;
-            rb.stats = nullptr;
-            rb.tmpl = h->tmpl[kLabelL];
-            int2* list = (int2*)(h->ds + o_list);
-            unsigned long long* dcount = (unsigned long long*)(h->ds + o_count);
-            const int grid = std::max(1, std::min(8 * h->cu_count, (n + bm::kGatherBlock - 1) / bm::kGatherBlock));
-            if ((r = check(h, bm::launch_gen_lines(lines, first_line + c0, n, seed, st), "training lines")) ||
-                (r = check(h, bm::launch_analytic(fb, st), "analytic")) ||
-                (r = check(h, bm::launch_label_entries(list, n, st), "label windows")) ||
-                (r = check(h, bm::launch_fill_u64(dcount, 1, (unsigned long long)n, st), "label count")) ||
-                (r = check(h, bm::launch_rootmusic_gather(kLabelL, rb, list, dcount, grid, st), "labels")) ||
-                (r = check(h, bm::launch_train_features(gamma, n, labels, X + c0 * bm::kMlpIn, T + c0 * bm::kMlpOut,
-                                                        st),
-                           "features")))
+            if ((r = check(h, bm::launch_train_set(first_line + c0, n, seed, h->tmpl[kLabelL],
+                                                   (h->options & BM_OPT_JACOBI) ? 1 : 0,
+                                                   (h->options & BM_OPT_FULL_ROOTS) ? 1 : 0, (float2*)h->ds,
+                                                   X + c0 * bm::kMlpIn, T + c0 * bm::kMlpOut,
+                                                   omega ? omega + c0 : nullptr, st),
+                           "training set")))
                 return r;
         }
         return check(h, hipStreamSynchronize(st), "dataset");

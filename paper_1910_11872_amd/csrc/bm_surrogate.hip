@@ -366,69 +366,180 @@ __device__ __forceinline__ uint4 philox4x32_10(uint4 c, uint2 k) {
             k.x += 0x9E3779B9u;
             k.y += 0xBB67AE85u;
         }
-        const uint32_t lo0 = 0xD2511F53u * c.x, hi0 = __umulhi(0xD2511F53u, c.x);
-        const uint32_t lo1 = 0xCD9E8D57u * c.z, hi1 = __umulhi(0xCD9E8D57u, c.z);
-        c = make_uint4(hi1 ^ c.y ^ k.x, lo1, hi0 ^ c.w ^ k.y, lo0);
+        const uint64_t p0 = (uint64_t)0xD2511F53u * c.x, p1 = (uint64_t)0xCD9E8D57u * c.z;
+        c = make_uint4((uint32_t)(p1 >> 32) ^ c.y ^ k.x, (uint32_t)p1, (uint32_t)(p0 >> 32) ^ c.w ^ k.y, (uint32_t)p0);
     }
     return c;
 }
 
 __device__ __forceinline__ float u01(uint32_t u) { return ((float)u + 0.5f) * 2.3283064365386963e-10f; }
 
-// Training line id (first + blockIdx.x): 0.5 + 0.4 cos(w n + theta) + noise,
+constexpr int kLineLen = 128, kDsLines = 64, kDsWin = 32, kDsFirst = 48;   // windows: samples 48 .. 79
+
+// Taps of the Hilbert transform of 128 periodic samples, the imaginary part of
+// the one-sided spectral mask: (2/128) cot(pi k / 128) at odd k = i - 80, else 0.
+__device__ const float kHilbert128[160] = {
+    0.f, 0.0060272276f, 0.f, 0.00516180277f, 0.f, 0.00432401985f, 0.f, 0.00350871108f,
+    0.f, 0.00271119469f, 0.f, 0.00192715994f, 0.f, 0.00115256924f, 0.f, 0.00038357222f,
+    0.f, -0.00038357222f, 0.f, -0.00115256924f, 0.f, -0.00192715994f, 0.f, -0.00271119469f,
+    0.f, -0.00350871108f, 0.f, -0.00432401985f, 0.f, -0.00516180277f, 0.f, -0.0060272276f,
+    0.f, -0.00692608615f, 0.f, -0.00786496406f, 0.f, -0.00885145317f, 0.f, -0.00989442213f,
+    0.f, -0.0110043666f, 0.f, -0.0121938697f, 0.f, -0.0134782177f, 0.f, -0.0148762367f,
+    0.f, -0.0164114507f, 0.f, -0.0181137173f, 0.f, -0.0200215872f, 0.f, -0.0221857954f,
+    0.f, -0.0246745714f, 0.f, -0.0275819823f, 0.f, -0.0310415436f, 0.f, -0.0352494352f,
+    0.f, -0.0405062893f, 0.f, -0.0472975501f, 0.f, -0.056461495f, 0.f, -0.0695812848f,
+    0.f, -0.0900490938f, 0.f, -0.126684153f, 0.f, -0.211822957f, 0.f, -0.636491936f,
+    0.f, 0.636491936f, 0.f, 0.211822957f, 0.f, 0.126684153f, 0.f, 0.0900490938f,
+    0.f, 0.0695812848f, 0.f, 0.056461495f, 0.f, 0.0472975501f, 0.f, 0.0405062893f,
+    0.f, 0.0352494352f, 0.f, 0.0310415436f, 0.f, 0.0275819823f, 0.f, 0.0246745714f,
+    0.f, 0.0221857954f, 0.f, 0.0200215872f, 0.f, 0.0181137173f, 0.f, 0.0164114507f,
+    0.f, 0.0148762367f, 0.f, 0.0134782177f, 0.f, 0.0121938697f, 0.f, 0.0110043666f,
+    0.f, 0.00989442213f, 0.f, 0.00885145317f, 0.f, 0.00786496406f, 0.f, 0.00692608615f,
+    0.f, 0.0060272276f, 0.f, 0.00516180277f, 0.f, 0.00432401985f, 0.f, 0.00350871108f,
+    0.f, 0.00271119469f, 0.f, 0.00192715994f, 0.f, 0.00115256924f, 0.f, 0.00038357222f,
+    0.f, -0.00038357222f, 0.f, -0.00115256924f, 0.f, -0.00192715994f, 0.f, -0.00271119469f,
+    0.f, -0.00350871108f, 0.f, -0.00432401985f, 0.f, -0.00516180277f, 0.f, -0.0060272276f,
+};
+
+// Training lines first .. first+count-1: 0.5 + 0.4 cos(w n + theta) + noise,
 // parameters from counter (id, 0, 0, 0), noise of samples 4b..4b+3 from
-// counter (id, b+1, 0, 0) by two Box-Muller pairs.  One block of 32 lanes per line.
-__global__ __launch_bounds__(32) void gen_lines_kernel(float* lines, long long first, unsigned long long seed) {
-    const uint32_t id = (uint32_t)(first + blockIdx.x);
+// counter (id, b+1, 0, 0) by two Box-Muller pairs; of their analytic signal the
+// label window, samples 48 .. 79, as gamma[k * pitch + line], and its features.
+// A block makes 64 lines and keeps them in LDS.  Only 32 samples of each line's
+// analytic signal are wanted, so their Hilbert transform is summed directly
+// (64 taps each, one line per lane, the taps in scalar registers) instead of by
+// two transforms of the whole line.  Bound by VALU issue: the generator's integer
+// products and elementary functions.  262144 lines, with their labels: 0.90 ms in
+// six launches (lines and analytic signal through device memory) -> 0.20 in two.
+__global__ __launch_bounds__(256) void train_lines_kernel(long long first, int count, unsigned long long seed,
+                                                           float2* gamma, int pitch, float* X) {
+    __shared__ float xs[kDsLines * (kLineLen + 1)];
+    __shared__ float2 gw[kDsLines * (kDsWin + 1)];
+    __shared__ float freq[kDsLines], theta[kDsLines], sigma[kDsLines];
+    __shared__ float2 rot[kDsLines];                            // feature factor
+    constexpr float kTwoPi = 6.28318530717958648f;
+    const int t = threadIdx.x;
+    const int l0 = blockIdx.x * kDsLines, nl = min(kDsLines, count - l0);
     const uint2 key = make_uint2((uint32_t)seed, (uint32_t)(seed >> 32));
-    const uint4 pr = philox4x32_10(make_uint4(id, 0u, 0u, 0u), key);
-    const float kTwoPi = 6.28318530717958648f;
-    const float w = kTwoPi / 16.f + u01(pr.x) * (kTwoPi / 4.f - kTwoPi / 16.f);
-    const float th = kTwoPi * u01(pr.y);
-    const float snr = 30.f * u01(pr.z);
-    const float sig = sqrtf(0.08f * exp10f(-0.1f * snr));
-    const int b = threadIdx.x;
-    const uint4 q = philox4x32_10(make_uint4(id, (uint32_t)b + 1u, 0u, 0u), key);
-    const float r0 = sqrtf(-2.f * logf(u01(q.x))), r1 = sqrtf(-2.f * logf(u01(q.z)));
-    float s0, c0, s1, c1;
-    sincosf(kTwoPi * u01(q.y), &s0, &c0);
-    sincosf(kTwoPi * u01(q.w), &s1, &c1);
-    const float z[4] = {r0 * c0, r0 * s0, r1 * c1, r1 * s1};
-    float* out = lines + (int64_t)blockIdx.x * 128;
+    const uint32_t id0 = (uint32_t)(first + l0);
+    if (t < kDsLines) {
+        const uint4 pr = philox4x32_10(make_uint4(id0 + t, 0u, 0u, 0u), key);
+        freq[t] = kTwoPi / 16.f + u01(pr.x) * (kTwoPi / 4.f - kTwoPi / 16.f);
+        theta[t] = kTwoPi * u01(pr.y);
+        sigma[t] = sqrtf(0.08f * exp10f(-0.1f * (30.f * u01(pr.z))));
+    }
+    __syncthreads();
+#pragma unroll 1
+    for (int e = t; e < kDsLines * (kLineLen / 4); e += 256) {
+        const int line = e >> 5, b = e & 31;
+        const uint4 q = philox4x32_10(make_uint4(id0 + line, (uint32_t)b + 1u, 0u, 0u), key);
+        const float r0 = sqrtf(-2.f * logf(u01(q.x))), r1 = sqrtf(-2.f * logf(u01(q.z)));
+        float s0, c0, s1, c1;
+        sincosf(kTwoPi * u01(q.y), &s0, &c0);
+        sincosf(kTwoPi * u01(q.w), &s1, &c1);
+        const float z[4] = {r0 * c0, r0 * s0, r1 * c1, r1 * s1};
+        const float w = freq[line], th = theta[line], sg = sigma[line];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int n = 4 * b + i;
-        out[n] = 0.5f + 0.4f * cosf(w * (float)n + th) + sig * z[i];
+        for (int i = 0; i < 4; ++i) {
+            const int n = 4 * b + i;
+            xs[line * (kLineLen + 1) + n] = 0.5f + 0.4f * cosf(w * (float)n + th) + sg * z[i];
+        }
+    }
+    __syncthreads();
+    // ---- the window's analytic signal: lane = line, eight samples per wave ----
+    const int lane = t & 63, wv = __builtin_amdgcn_readfirstlane(t >> 6);
+    {
+        const int n0 = kDsFirst + 8 * wv;
+        const float* x = xs + lane * (kLineLen + 1);
+        float im[8], even = 0.f, odd = 0.f;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) im[i] = 0.f;
+#pragma unroll 1
+        for (int m0 = 0; m0 < kLineLen; m0 += 8) {
+            const float* tap = kHilbert128 + (n0 - m0 + 80 - 7);
+            float tp[15];
+#pragma unroll
+            for (int i = 0; i < 15; ++i) tp[i] = tap[i];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const float v = x[m0 + j];
+                if (j & 1) odd += v;
+                else even += v;
+#pragma unroll
+                for (int i = 0; i < 8; ++i)
+                    if ((i ^ j) & 1) im[i] = fmaf(v, tp[7 + i - j], im[i]);
+            }
+        }
+        const float dc = (even + odd) * (1.f / kLineLen), ny = (even - odd) * (1.f / kLineLen);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const float2 v = make_float2(x[n0 + i] - dc - ((i & 1) ? -ny : ny), im[i]);
+            gw[lane * (kDsWin + 1) + 8 * wv + i] = v;
+            if (lane < nl) gamma[(int64_t)(8 * wv + i) * pitch + l0 + lane] = v;
+        }
+    }
+    __syncthreads();
+    // ---- features: 16 central samples, de-rotated by the central one, over the RMS
+    if (t < kDsLines) {
+        const float2* w = gw + t * (kDsWin + 1);
+        float e = 0.f;
+        for (int k = 0; k < kDsWin; ++k) e = fmaf(w[k].x, w[k].x, fmaf(w[k].y, w[k].y, e));
+        const float2 gc = w[16];
+        const float mc = sqrtf(gc.x * gc.x + gc.y * gc.y);
+        const float sc = (mc > 0.f && e > 0.f) ? 1.f / (mc * sqrtf(e / 32.f)) : 0.f;
+        rot[t] = make_float2(gc.x * sc, -gc.y * sc);
+    }
+    __syncthreads();
+    for (int e = t; e < nl * kMlpIn; e += 256) {
+        const int line = e >> 5, i = e & 31;
+        const float2 v = gw[line * (kDsWin + 1) + 8 + (i & 15)], r = rot[line];
+        X[(int64_t)l0 * kMlpIn + e] = i < 16 ? v.x * r.x - v.y * r.y : v.x * r.y + v.y * r.x;
     }
 }
 
-// Entries {job, line << 16 | 64} of the label windows (centre of each line),
-// 65536 lines per job.
-__global__ void label_entries_kernel(int2* list, int count) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < count) list[i] = make_int2(i >> 16, (int)(((unsigned)(i & 0xFFFF) << 16) | 64u));
-}
-
-// Features of the 32-sample window centred on sample 64 of each line, and the
-// target (cos w, sin w) of its label.
-__global__ void train_features_kernel(const float2* gamma, int count, const float* labels, float* X, float* T) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+// Labels and targets: the plain root-MUSIC frequency (L = 8) of each window
+// gamma[k * pitch + i], one per lane, and (cos, sin) of it.  The covariance's
+// lag sums of the window's eight starts share their products (the common ones
+// once, the others added from either side; nothing is subtracted).
+template <bool JACOBI>
+__global__ __launch_bounds__(64) void train_labels_kernel(const float2* gamma, int pitch, int count, RootTemplate tmpl,
+                                                           int full_roots, float* labels, float* T) {
+    constexpr int L = 8, K = kDsWin - L + 1;
+    const int i = blockIdx.x * 64 + threadIdx.x;
     if (i >= count) return;
-    const float2* w = gamma + (int64_t)i * 128 + 48;
-    float e = 0.f;
-    for (int k = 0; k < 32; ++k) e = fmaf(w[k].x, w[k].x, fmaf(w[k].y, w[k].y, e));
-    const float2 gc = w[16];
-    const float mc = sqrtf(gc.x * gc.x + gc.y * gc.y);
-    const float sc = (mc > 0.f && e > 0.f) ? 1.f / (mc * sqrtf(e / 32.f)) : 0.f;
-    const float rc = gc.x * sc, rs = -gc.y * sc;
-    float* x = X + (int64_t)i * kMlpIn;
-    for (int k = 0; k < 16; ++k) {
-        const float2 v = w[8 + k];
-        x[k] = v.x * rc - v.y * rs;
-        x[16 + k] = v.x * rs + v.y * rc;
+    float2 g[kDsWin];
+#pragma unroll
+    for (int k = 0; k < kDsWin; ++k) g[k] = gamma[(int64_t)k * pitch + i];
+    Cov<L> R;
+#pragma unroll
+    for (int d = 0; d < L; ++d) {
+        auto add = [&](int k, float2& s) {
+            s.x = fmaf(g[k].x, g[k + d].x, fmaf(g[k].y, g[k + d].y, s.x));
+            s.y = fmaf(g[k].y, g[k + d].x, fmaf(-g[k].x, g[k + d].y, s.y));
+        };
+        float2 s = make_float2(0.f, 0.f), up = make_float2(0.f, 0.f);
+#pragma unroll
+        for (int k = L - 1 - d; k < K; ++k) add(k, s);
+#pragma unroll
+        for (int j = L - 1 - d; j >= 0; --j) {
+            if (j < L - 1 - d) add(j, s);
+            R.re[j][j + d] = s.x;
+            R.im[j][j + d] = d == 0 ? 0.f : s.y;
+        }
+#pragma unroll
+        for (int j = 1; j <= L - 1 - d; ++j) {
+            add(K - 1 + j, up);
+            R.re[j][j + d] += up.x;
+            if (d > 0) R.im[j][j + d] += up.y;
+        }
     }
+    float omega = __builtin_nanf("");
+    unsigned flag = 0;
+    LaneStats ls;
+    window_omega<L, JACOBI>(R, tmpl, full_roots != 0, K, __builtin_nanf(""), omega, flag, ls);
+    if (labels) labels[i] = omega;
     float sw, cw;
-    sincosf(labels[i], &sw, &cw);
+    sincosf(omega, &sw, &cw);
     T[2 * (int64_t)i] = cw;
     T[2 * (int64_t)i + 1] = sw;
 }
@@ -745,11 +856,6 @@ __global__ __launch_bounds__(256) void mlp_reduce_adam_kernel(const float* part,
     } else if (kind == 3) wts[2048 + 4096 + o * 64 + i] = bv;             // W3^T
 }
 
-__global__ void fill_u64_kernel(unsigned long long* p, int n, unsigned long long v) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = v;
-}
-
 }  // namespace
 
 template <int L>
@@ -781,22 +887,18 @@ hipError_t launch_mlp_forward(const MlpWeights& w, const float* X, float* Y, int
 }
 
 
-hipError_t launch_gen_lines(float* lines, long long first, int count, unsigned long long seed, hipStream_t s) {
+hipError_t launch_train_set(long long first, int count, unsigned long long seed, const RootTemplate& tmpl, int jacobi,
+                            int full_roots, float2* gamma, float* X, float* T, float* labels, hipStream_t s) {
     if (count <= 0) return hipSuccess;
-    hipLaunchKernelGGL(gen_lines_kernel, dim3(count), dim3(32), 0, s, lines, first, seed);
-    return hipGetLastError();
-}
-
-hipError_t launch_label_entries(int2* list, int count, hipStream_t s) {
-    if (count <= 0) return hipSuccess;
-    hipLaunchKernelGGL(label_entries_kernel, dim3((count + 255) / 256), dim3(256), 0, s, list, count);
-    return hipGetLastError();
-}
-
-hipError_t launch_train_features(const float2* gamma, int count, const float* labels, float* X, float* T,
-                                 hipStream_t s) {
-    if (count <= 0) return hipSuccess;
-    hipLaunchKernelGGL(train_features_kernel, dim3((count + 255) / 256), dim3(256), 0, s, gamma, count, labels, X, T);
+    hipLaunchKernelGGL(train_lines_kernel, dim3((count + kDsLines - 1) / kDsLines), dim3(256), 0, s, first, count, seed,
+                       gamma, count, X);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    const dim3 grid((count + 63) / 64), block(64);
+    if (jacobi) hipLaunchKernelGGL(train_labels_kernel<true>, grid, block, 0, s, gamma, count, count, tmpl, full_roots,
+                                   labels, T);
+    else hipLaunchKernelGGL(train_labels_kernel<false>, grid, block, 0, s, gamma, count, count, tmpl, full_roots, labels,
+                            T);
     return hipGetLastError();
 }
 
@@ -813,12 +915,6 @@ hipError_t launch_mlp_reduce_adam(const float* part, int nblocks, float* master,
                                   float* loss, __bf16* wts, int adam, float lr, float c1, float c2, hipStream_t s) {
     hipLaunchKernelGGL(mlp_reduce_adam_kernel, dim3((kPartLoss + 1 + kReduceItems - 1) / kReduceItems), dim3(256), 0, s,
                        part, nblocks, master, m, v, grad, loss, wts, adam, lr, c1, c2);
-    return hipGetLastError();
-}
-
-hipError_t launch_fill_u64(unsigned long long* p, int n, unsigned long long v, hipStream_t s) {
-    if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(fill_u64_kernel, dim3((n + 255) / 256), dim3(256), 0, s, p, n, v);
     return hipGetLastError();
 }
 

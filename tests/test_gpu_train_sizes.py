@@ -3,7 +3,10 @@ second walk, and sample buffers that are only 4-byte aligned."""
 import numpy as np
 import pytest
 
+import oracle
+import workloads as wl
 from oracle import surrogate as S
+from parity_util import OMEGA_TOL, wrap
 
 pytestmark = pytest.mark.gpu
 
@@ -43,3 +46,28 @@ def test_gradient_sizes_and_alignment(bm, M):
         off += n
         # bfloat16 operands: 2^-9 per factor, as the tolerance of the larger batch
         assert np.linalg.norm(a - b) <= 1e-2 * np.linalg.norm(b), k
+
+
+@pytest.mark.parametrize("count", [1, 63, 64, 65, 200])
+def test_dataset_sizes(bm, count):
+    """Blocks of 64 lines: partial ones give the lines of a longer set, which match the oracle."""
+    import torch
+    d = bm.Demodulator(0, max_width=64, max_height=64)
+
+    def dataset(first, n):
+        X, T, w = (torch.full(s, 7.0, device="cuda") for s in ((n + 1, 32), (n + 1, 2), (n + 1,)))
+        bm.bosmusic_surrogate_dataset(d.h, first, X[:n], T[:n], w[:n], seed=5)
+        for t in (X, T, w):
+            assert bool((t[n:] == 7.0).all())               # nothing is written past the end
+        return X[:n].cpu().numpy(), T[:n].cpu().numpy(), w[:n].cpu().numpy()
+
+    got, long = dataset(1000, count), dataset(900, 500)
+    d.close()
+    for a, b in zip(got, long):
+        assert np.array_equal(a, b[100:100 + count])
+    lines, _ = wl.philox_training_lines(np.arange(1000, 1000 + count), 5)
+    win = oracle.analytic_signal(lines)[:, 48:80]
+    omega = oracle.demod_windows(win, 8)
+    assert np.max(np.abs(got[0] - S.features(win))) < 2e-4
+    assert np.mean(np.abs(wrap(got[2].astype(np.float64) - omega)) > OMEGA_TOL) <= 0.01
+    assert np.max(np.abs(got[1] - np.stack([np.cos(got[2]), np.sin(got[2])], 1))) < 1e-6
