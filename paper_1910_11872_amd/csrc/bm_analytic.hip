@@ -11,11 +11,11 @@
 // their DC and Nyquist components removed.  Two transforms per pair of lines.  Twiddles come from per-pass tables of each length,
 // contiguous in the butterfly index, computed in FP64 on the host and
 // rounded once; they are read through the caches (staging them in LDS cost
-// more in blocks per CU than it saved in latency).  A length with a prime factor above 13 takes each DFT
-// by Bluestein's identity jk = (j^2 + k^2 - (k-j)^2) / 2: with the chirp
-// w_j = e^{-i pi j^2 / n}, X_k = w_k sum_j (x_j w_j) conj(w_{k-j}), a linear
-// convolution done as a circular one of 5-smooth length m >= 2n - 1 (two
-// length-m FFTs against the precomputed transform of the conjugate chirp).
+// more in blocks per CU than it saved in latency).  A length n with a prime factor
+// above 13 takes the Hilbert transform as the circular convolution that it is:
+// the samples padded with zeros to m >= 2n - 1, a transform of length m,
+// multiplied by that of the wrapped taps (-i times a real table, in the place of
+// -i sgn(k)), and a transform back.
 #include "bm_internal.h"
 
 namespace bm {
@@ -168,33 +168,6 @@ __device__ __forceinline__ float2* fft_forward(float2* a, float2* b, int n, cons
     return a;
 }
 
-// DFT of the n samples at a[0..n): a direct mixed-radix FFT, or Bluestein's
-// chirp-z route through length plan.n = m.  a and b hold m elements each;
-// returns the buffer holding X[0..n) in natural order.
-template <int MAXR, int T>
-__device__ __forceinline__ float2* dft_line(float2* a, float2* b, const FftJob& J, const float2* tw) {
-    const int n = J.n, m = J.plan.n;
-    if (!J.chirp) return fft_forward<MAXR, T>(a, b, n, J.plan, tw);
-    for (int i = threadIdx.x; i < m; i += T)
-        a[i] = i < n ? cmul(a[i], J.chirp[i]) : make_float2(0.f, 0.f);
-    __syncthreads();
-    float2* P = fft_forward<MAXR, T>(a, b, m, J.plan, tw);
-    float2* Q = (P == a) ? b : a;
-    // circular convolution with conj(w): inverse DFT as the conjugate of a forward one
-    for (int k = threadIdx.x; k < m; k += T) {
-        const float2 v = cmul(P[k], J.kern[k]);
-        P[k] = make_float2(v.x, -v.y);
-    }
-    __syncthreads();
-    float2* Y = fft_forward<MAXR, T>(P, Q, m, J.plan, tw);
-    for (int k = threadIdx.x; k < n; k += T) {
-        const float2 v = Y[k];
-        Y[k] = cmul(make_float2(v.x, -v.y), J.chirp[k]);
-    }
-    __syncthreads();
-    return Y;
-}
-
 // Index of the job that owns work item w: prefix[j] <= w < prefix[j+1].
 __device__ __forceinline__ int find_job(const int* prefix, int njobs, int w) {
     int lo = 0, hi = njobs - 1;
@@ -249,23 +222,26 @@ __global__ __launch_bounds__(T) void analytic_kernel(FftBatch B, int item0) {
     float2* b = lds + m;
     const float2* tw = J.tw;
     const int64_t off = (int64_t)la * J.src_ls;
-    for (int i = threadIdx.x; i < n; i += T)
-        a[i] = make_float2(load_real(J.src, off + i, elem), two ? load_real(J.src, off + J.src_ls + i, elem) : 0.f);
+    for (int i = threadIdx.x; i < m; i += T)       // m = n, or zeros beyond n for the convolution
+        a[i] = i < n ? make_float2(load_real(J.src, off + i, elem),
+                                   two ? load_real(J.src, off + J.src_ls + i, elem) : 0.f)
+                     : make_float2(0.f, 0.f);
     __syncthreads();
-    float2* X = dft_line<MAXR, T>(a, b, J, tw);
+    float2* X = fft_forward<MAXR, T>(a, b, m, J.plan, tw);
     float2* V = (X == a) ? b : a;
     const float inv_n = 1.0f / (float)n;
     const float2 z0 = X[0];
-    const float2 zh = (n & 1) ? make_float2(0.f, 0.f) : X[n >> 1];
+    const float2 zh = (n & 1) ? make_float2(0.f, 0.f) : X[m >> 1];
     // V = conj(-i sgn(k) Z[k]) / n = sgn(k) (Im Z, Re Z) / n, so that the forward DFT
-    // of V, conjugated, is IFFT(-i sgn Z)
-    for (int k = threadIdx.x; k < n; k += T) {
+    // of V, conjugated, is IFFT(-i sgn Z); with the convolution's table for sgn(k) / n
+    const float* conv = J.conv;
+    for (int k = threadIdx.x; k < m; k += T) {
         const float2 v = X[k];
-        const float sg = (k == 0 || 2 * k == n) ? 0.f : (2 * k < n ? inv_n : -inv_n);
+        const float sg = conv ? conv[k] : (k == 0 || 2 * k == n) ? 0.f : (2 * k < n ? inv_n : -inv_n);
         V[k] = make_float2(sg * v.y, sg * v.x);
     }
     __syncthreads();
-    float2* Y = dft_line<MAXR, T>(V, X, J, tw);
+    float2* Y = fft_forward<MAXR, T>(V, X, m, J.plan, tw);
     // h_a + i h_b = conj(Y): Im Gamma_a = Y.x, Im Gamma_b = -Y.y
     const float dca = z0.x * inv_n, dcb = z0.y * inv_n, nqa = zh.x * inv_n, nqb = zh.y * inv_n;
     float2* out = J.dst + (int64_t)la * n;
@@ -280,9 +256,9 @@ __global__ __launch_bounds__(T) void analytic_kernel(FftBatch B, int item0) {
     }
 }
 
-// ---- power-of-two lines of 512 ... 4096 samples: register-resident passes ----
+// ---- power-of-two transforms of 512 ... 4096 samples: register-resident passes ----
 //
-// n = R0 * 256 with R0 in {2, 4, 8, 16} takes three Stockham passes of radices
+// n = R0 * 256 (a line, or a convolution's padded length) with R0 in {2, 4, 8, 16} takes three Stockham passes of radices
 // R0, 16, 16 (the pass formulas of stockham_pass).  A line pair is n/16
 // threads, and in every pass thread j holds the 16 elements j + s n/16,
 // s < 16, of the transform in registers: the first pass reads them straight
@@ -435,19 +411,23 @@ __device__ __forceinline__ void pow2_fft(float2 (&z)[16], float2* buf, int base,
     pow2_pass16(z, tw2, T, j);
 }
 
-// The analytic signal of analytic_kernel for n = 256 R0, per line pair:
-// Z = DFT(x_a + i x_b), V = sgn(k) (Im Z, Re Z) / n, Y = DFT(V); Im Gamma_a =
-// Y.x, Im Gamma_b = -Y.y, Re Gamma = x - DC - Nyquist (-1)^i.
-template <int R0>
-__global__ __launch_bounds__(256) void analytic_pow2_kernel(FftBatch B, int item0) {
-    constexpr int n = 256 * R0, T = 16 * R0, P = 4096 / n;
+// The analytic signal of analytic_kernel for transforms of m = 256 R0, per line
+// pair: Z = DFT(x_a + i x_b), V = sgn(k) (Im Z, Re Z) / n, Y = DFT(V); Im Gamma_a
+// = Y.x, Im Gamma_b = -Y.y, Re Gamma = x - DC - Nyquist (-1)^i.  CONV: lines of
+// n <= m/2 samples, zeros beyond them and the convolution's table for sgn(k) / n;
+// DC and Nyquist are the bins 0 and m/2 all the same.
+template <int R0, bool CONV>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CONV && R0 >= 8 ? 4 : 1)))
+void analytic_pow2_kernel(FftBatch B, int item0) {
+    constexpr int m = 256 * R0, T = 16 * R0, P = 4096 / m;
     __shared__ float2 buf[4096];
     const int w = item0 + blockIdx.x;
     const int jb = find_job(B.prefix, B.njobs, w);
     const FftJob& J = B.jobs[jb];
     const int item = w - B.prefix[jb];
     const int t = threadIdx.x, p = t / T, j = t - p * T;
-    const int base = p * n;
+    const int base = p * m;
+    const int n = CONV ? J.n : m;
     const int la = 2 * (item * P + p);
     const bool has_a = la < J.nlines, has_b = la + 1 < J.nlines;
     const int elem = J.elem;
@@ -456,17 +436,17 @@ __global__ __launch_bounds__(256) void analytic_pow2_kernel(FftBatch B, int item
 #pragma unroll
     for (int s = 0; s < 16; ++s) {
         const int i = j + s * T;
-        z[s] = make_float2(has_a ? load_real(J.src, off + i, elem) : 0.f,
-                           has_b ? load_real(J.src, off + J.src_ls + i, elem) : 0.f);
+        z[s] = make_float2(has_a && (!CONV || i < n) ? load_real(J.src, off + i, elem) : 0.f,
+                           has_b && (!CONV || i < n) ? load_real(J.src, off + J.src_ls + i, elem) : 0.f);
     }
     pow2_fft<R0>(z, buf, base, j, J.tw);
     // z[s] = Z[j + s T]; DC at (j, s) = (0, 0), Nyquist at (0, 8)
-    const float2 z0 = z[0], zh = z[8];
-    constexpr float inv_n = 1.0f / (float)n;
+    const float2 z0 = z[0], zh = CONV && (n & 1) ? make_float2(0.f, 0.f) : z[8];
+    const float inv_n = 1.0f / (float)n;
 #pragma unroll
     for (int s = 0; s < 16; ++s) {
         const int k = j + s * T;
-        const float sg = (k == 0 || 2 * k == n) ? 0.f : (2 * k < n ? inv_n : -inv_n);
+        const float sg = CONV ? J.conv[k] : (k == 0 || 2 * k == n) ? 0.f : (2 * k < n ? inv_n : -inv_n);
         z[s] = make_float2(sg * z[s].y, sg * z[s].x);
     }
     __syncthreads();
@@ -484,6 +464,7 @@ __global__ __launch_bounds__(256) void analytic_pow2_kernel(FftBatch B, int item
 #pragma unroll
     for (int s = 0; s < 16; ++s) {
         const int i = j + s * T;
+        if (CONV && i >= n) break;
         const float sgn = (i & 1) ? -1.f : 1.f;
         if (has_a) __builtin_nontemporal_store(f2v{load_real(J.src, off + i, elem) - dca - sgn * nqa, z[s].x},
                                                reinterpret_cast<f2v*>(out + i));
@@ -585,6 +566,11 @@ hipError_t analytic_set_attributes() {
     return hipSuccess;
 }
 
+template <int R0, bool CONV>
+static void launch_pow2(const FftBatch& b, int item0, int items, hipStream_t s) {
+    hipLaunchKernelGGL((analytic_pow2_kernel<R0, CONV>), dim3(items), dim3(256), 0, s, b, item0);
+}
+
 hipError_t launch_analytic(const FftBatch& b, hipStream_t s) {
     for (int c = 0; c < kFftClasses; ++c) {
         const int i0 = b.cls_from[c], cnt = b.cls_from[c + 1] - i0;
@@ -595,10 +581,14 @@ hipError_t launch_analytic(const FftBatch& b, hipStream_t s) {
             case 1: hipLaunchKernelGGL((analytic_kernel<13, 256>), dim3(cnt), dim3(256), shmem, s, b, i0); break;
             case 2: hipLaunchKernelGGL((analytic_kernel<5, 1024>), dim3(cnt), dim3(1024), shmem, s, b, i0); break;
             case 3: hipLaunchKernelGGL((analytic_kernel<13, 1024>), dim3(cnt), dim3(1024), shmem, s, b, i0); break;
-            case 4: hipLaunchKernelGGL((analytic_pow2_kernel<2>), dim3(cnt), dim3(256), 0, s, b, i0); break;
-            case 5: hipLaunchKernelGGL((analytic_pow2_kernel<4>), dim3(cnt), dim3(256), 0, s, b, i0); break;
-            case 6: hipLaunchKernelGGL((analytic_pow2_kernel<8>), dim3(cnt), dim3(256), 0, s, b, i0); break;
-            default: hipLaunchKernelGGL((analytic_pow2_kernel<16>), dim3(cnt), dim3(256), 0, s, b, i0); break;
+            case 4: launch_pow2<2, false>(b, i0, cnt, s); break;
+            case 5: launch_pow2<4, false>(b, i0, cnt, s); break;
+            case 6: launch_pow2<8, false>(b, i0, cnt, s); break;
+            case 7: launch_pow2<16, false>(b, i0, cnt, s); break;
+            case 8: launch_pow2<2, true>(b, i0, cnt, s); break;
+            case 9: launch_pow2<4, true>(b, i0, cnt, s); break;
+            case 10: launch_pow2<8, true>(b, i0, cnt, s); break;
+            default: launch_pow2<16, true>(b, i0, cnt, s);
         }
     }
     return hipGetLastError();

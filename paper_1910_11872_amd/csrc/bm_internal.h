@@ -92,35 +92,36 @@ struct RmBatch {
 };
 
 // Lines of one frame direction for the analytic-signal kernel (one block per line).
-// A length n with a prime factor above 13 takes the DFT by Bluestein's chirp-z
-// identity through a circular convolution of 5-smooth length m = plan.n >= 2n-1.
+// A length n with a prime factor above 13 takes the Hilbert transform as the
+// circular convolution that it is, embedded in one of length m = plan.n >= 2n-1
+// (even): 5-smooth, or a power of two on the register-resident path.
 struct FftJob {
     const void* src;       // real lines, src_ls elements apart
     int64_t src_ls;
     float2* dst;           // complex lines, n apart
     const float2* tw;      // per-pass twiddle tables of plan.n (read from global memory: cached,
                            // and leaving LDS to more blocks measured faster than staging them)
-    const float2* chirp;   // Bluestein only: e^{-i pi j^2 / n}, j < n
-    const float2* kern;    // Bluestein only: DFT_m of the conjugate chirp, wrapped, divided by m
+    const float* conv;     // convolution only: i/m times the DFT_m of the Hilbert taps of n samples
+                           // (real), else nullptr
     int elem;              // Elem of src
     int nlines;
     int n;                 // line length
-    FftPlan plan;          // plan of n, or of m under Bluestein (chirp != nullptr)
-    int pow2;              // R0 of the register-resident path (n = 256 R0, R0 in 2, 4, 8, 16;
+    FftPlan plan;          // plan of n, or of m with conv
+    int pow2;              // R0 of the register-resident path (plan.n = 256 R0, R0 in 2, 4, 8, 16;
                            // plan = R0, 16, 16), 0 for the LDS Stockham path
 };
 
-// The register-resident path takes n = 256 R0, R0 in {2, 4, 8, 16}.
+// The register-resident path takes transforms of 256 R0, R0 in {2, 4, 8, 16}.
 inline int fft_pow2_r0(int n) { return (n == 512 || n == 1024 || n == 2048 || n == 4096) ? n / 256 : 0; }
 
 // LDS of the analytic kernel's block, in complex elements (132 KiB): two
-// buffers of up to 8192 samples (or of a Bluestein transform length).
+// buffers of up to 8192 samples (or of a convolution's transform length).
 constexpr int kFftLdsElems = 16896;
 
 // Transform lengths above this run 1024 threads per block, shorter ones 256.
 constexpr int kFftWideMin = 2049;
 
-// Work items (blocks) of one job: pairs of lines, 4096/n pairs per block on
+// Work items (blocks) of one job: pairs of lines, 16 / R0 pairs per block on
 // the register-resident path.
 inline int fft_items(const FftJob& j) {
     const int pairs = (j.nlines + 1) / 2;
@@ -152,13 +153,14 @@ inline bool fft_big_radix(const FftJob& j) {
 }
 
 // Kernel variant of a job: radices up to 5, or up to 13; 256 or 1024 threads;
-// or the register-resident path of R0 = 2, 4, 8, 16 (classes 4 .. 7).
-constexpr int kFftClasses = 8;
+// or the register-resident path of R0 = 2, 4, 8, 16 (classes 4 .. 7, as a
+// convolution 8 .. 11).
+constexpr int kFftClasses = 12;
 // A job of the 1024-thread kernel variants (classes 2 and 3).
 inline bool fft_wide(const FftJob& j) { return !j.pow2 && j.plan.n >= kFftWideMin; }
 
 inline int fft_class(const FftJob& j) {
-    if (j.pow2) return j.pow2 == 2 ? 4 : j.pow2 == 4 ? 5 : j.pow2 == 8 ? 6 : 7;
+    if (j.pow2) return (j.pow2 == 2 ? 4 : j.pow2 == 4 ? 5 : j.pow2 == 8 ? 6 : 7) + (j.conv ? 4 : 0);
     return (fft_big_radix(j) ? 1 : 0) + (j.plan.n >= kFftWideMin ? 2 : 0);
 }
 

@@ -49,7 +49,7 @@ struct bosmusic_s {
     double* anchor = nullptr;     // integration anchor column (max_h)
     unsigned long long* stats = nullptr;
     std::map<int, float2*> twiddles;
-    std::map<int, float2*> bluestein;   // line length -> chirp (n) then kernel (m) in one allocation
+    std::map<std::pair<int, int>, float*> conv;   // (line length, transform length) -> convolution table
     std::vector<std::pair<hipEvent_t, hipEvent_t>> ev_free, ev_pending;
     uint64_t rm_launches = 0, rm_time_ns = 0;
     bm::RootTemplate tmpl[bm::kMaxBlockL + 1];
@@ -178,11 +178,12 @@ bool fft_direct(int n) {
     return plan_fft(n, p);
 }
 
-// Transform length of Bluestein's route for a line of n samples: the least
-// 5-smooth m >= 2n - 1 (radix 2-5 passes only), or 0 when that exceeds the
+// Transform length of the convolution route for a line of n samples, at least
+// 2n - 1 and even (the line's Nyquist component is then the bin m/2 of its
+// padded transform): the least even 5-smooth one, or 0 when that exceeds the
 // largest FFT.
-int bluestein_len(int n) {
-    for (int m = std::max(2 * n - 1, 1); m <= bm::kMaxFFT; ++m) {
+int conv_len(int n) {
+    for (int m = 2 * n; m <= bm::kMaxFFT; m += 2) {
         int r = m;
         for (int f : {2, 3, 5})
             while (r % f == 0) r /= f;
@@ -191,8 +192,21 @@ int bluestein_len(int n) {
     return 0;
 }
 
-// A line of n samples has an exact DFT here: directly or by Bluestein.
-bool dft_supported(int n) { return n >= 1 && (fft_direct(n) || bluestein_len(n) > 0); }
+// The power of two of the register-resident path for it, 512 .. 4096, or 0.
+// It pays for frames of many lines (2^21 padded samples): 2048 lines of 1031
+// samples 80 -> 69 us, 8192 of 101 59 -> 50 (the whole call), equal near 2^21;
+// below, the 5-smooth lengths share one launch with each other and with the
+// direct transforms (331 x 85, both directions: 54 us with two launches, 50 with one).
+int conv_pow2_len(int n, int nlines) {
+    if (n > 2048) return 0;
+    int m = 512;
+    while (m < 2 * n - 1) m *= 2;
+    return (int64_t)m * nlines >= ((int64_t)1 << 21) ? m : 0;
+}
+
+// A line of n samples has an exact analytic signal here: by direct transforms
+// or by convolution.
+bool dft_supported(int n) { return n >= 1 && (fft_direct(n) || conv_len(n) > 0); }
 
 // In-place FP64 DFT (recursive decimation in time by the smallest prime factor).
 void dft64(std::vector<std::complex<double>>& x) {
@@ -312,60 +326,65 @@ bm_status get_twiddles(bosmusic_s* h, int n, const float2** out, int pow2 = 0) {
     return BM_OK;
 }
 
-// Chirp w_j = e^{-i pi j^2 / n} (j < n) and the length-m DFT of the wrapped
-// conjugate chirp c_t = conj(w_t), |t| < n, divided by m; computed in FP64
-// (the angle reduced exactly as j^2 mod 2n) and rounded once.
-bm_status get_bluestein(bosmusic_s* h, int n, int m, const float2** chirp, const float2** kern) {
-    auto it = h->bluestein.find(n);
-    if (it == h->bluestein.end()) {
+// The Hilbert transform of n periodic samples (the spectrum times -i sgn k, 0 at
+// DC and Nyquist) is a circular convolution with the odd taps
+//   t_j = (2/n) sum_{0 < k < n/2} sin(2 pi k j / n)
+//       = (cos(pi j/n) - (-1)^j g) / (n sin(pi j/n)),  g = cos(pi j/n) for even n, 1 for odd n.
+// Wrapped to length m >= 2n - 1 (t_j at j and -t_j at m - j) their DFT is -i
+// times a real S; the table holds S / m, computed in FP64 and rounded once.
+bm_status get_conv(bosmusic_s* h, int n, int m, const float** out) {
+    auto it = h->conv.find({n, m});
+    if (it == h->conv.end()) {
         using cd = std::complex<double>;
-        std::vector<cd> w(n), c(m, cd(0.0, 0.0));
-        for (int j = 0; j < n; ++j) {
-            const int64_t r = ((int64_t)j * j) % (2 * (int64_t)n);
-            const double a = -M_PI * (double)r / (double)n;
-            w[j] = cd(std::cos(a), std::sin(a));
-        }
-        for (int t = 0; t < n; ++t) {
-            c[t] = std::conj(w[t]);
-            if (t > 0) c[m - t] = std::conj(w[t]);
+        std::vector<cd> c(m, cd(0.0, 0.0));
+        for (int j = 1; j < n; ++j) {
+            const double a = M_PI * (double)j / (double)n;
+            const double g = (n & 1) ? 1.0 : std::cos(a);
+            const double t = (std::cos(a) - ((j & 1) ? -g : g)) / ((double)n * std::sin(a));
+            c[j] += t;
+            c[m - j] -= t;
         }
         dft64(c);
-        std::vector<float2> host((size_t)n + m);
-        for (int j = 0; j < n; ++j) host[j] = make_float2((float)w[j].real(), (float)w[j].imag());
-        for (int k = 0; k < m; ++k)
-            host[(size_t)n + k] = make_float2((float)(c[k].real() / m), (float)(c[k].imag() / m));
-        float2* d = nullptr;
-        if (hipMalloc(&d, sizeof(float2) * host.size()) != hipSuccess)
-            return fail(h, BM_E_NOMEM, "Bluestein tables of %d", n);
-        if (hipMemcpy(d, host.data(), sizeof(float2) * host.size(), hipMemcpyHostToDevice) != hipSuccess) {
+        std::vector<float> host(m);
+        for (int k = 0; k < m; ++k) host[k] = (float)(-c[k].imag() / m);
+        float* d = nullptr;
+        if (hipMalloc(&d, sizeof(float) * host.size()) != hipSuccess)
+            return fail(h, BM_E_NOMEM, "convolution table of %d", n);
+        if (hipMemcpy(d, host.data(), sizeof(float) * host.size(), hipMemcpyHostToDevice) != hipSuccess) {
             (void)hipFree(d);
-            return fail(h, BM_E_DEVICE, "Bluestein table upload failed");
+            return fail(h, BM_E_DEVICE, "convolution table upload failed");
         }
-        it = h->bluestein.emplace(n, d).first;
+        it = h->conv.emplace(std::make_pair(n, m), d).first;
     }
-    *chirp = it->second;
-    *kern = it->second + n;
+    *out = it->second;
     return BM_OK;
 }
 
-// Plan, twiddles and (when n is not 13-smooth) Bluestein tables of a line length.
-bm_status make_fft_job(bosmusic_s* h, int n, bm::FftJob& fj) {
+bm_status make_fft_job(bosmusic_s* h, int n, int nlines, bm::FftJob& fj) {
     fj.n = n;
-    fj.chirp = fj.kern = nullptr;
-    fj.pow2 = bm::fft_pow2_r0(n);
-    if (fj.pow2) {
-        fj.plan.n = n;
+    fj.nlines = nlines;
+    fj.conv = nullptr;
+    auto pow2_plan = [&](int m) {
+        fj.plan.n = m;
         fj.plan.passes = 3;
         fj.plan.radix[0] = fj.pow2;
         fj.plan.radix[1] = fj.plan.radix[2] = 16;
-        return get_twiddles(h, n, &fj.tw, fj.pow2);
-    }
+        return get_twiddles(h, m, &fj.tw, fj.pow2);
+    };
+    fj.pow2 = bm::fft_pow2_r0(n);
+    if (fj.pow2) return pow2_plan(n);
     if (plan_fft(n, fj.plan)) return get_twiddles(h, n, &fj.tw);
-    const int m = bluestein_len(n);
-    if (m == 0 || !plan_fft(m, fj.plan)) return fail(h, BM_E_UNSUPPORTED, "line length %d", n);
-    bm_status st = get_twiddles(h, m, &fj.tw);
-    if (st != BM_OK) return st;
-    return get_bluestein(h, n, m, &fj.chirp, &fj.kern);
+    int m = conv_pow2_len(n, nlines);
+    fj.pow2 = m / 256;
+    bm_status st;
+    if (fj.pow2) {
+        st = pow2_plan(m);
+    } else {
+        m = conv_len(n);
+        if (m == 0 || !plan_fft(m, fj.plan)) return fail(h, BM_E_UNSUPPORTED, "line length %d", n);
+        st = get_twiddles(h, m, &fj.tw);
+    }
+    return st != BM_OK ? st : get_conv(h, n, m, &fj.conv);
 }
 
 bm_status validate_frame(bosmusic_s* h, const bosmusic_frame& f, int idx) {
@@ -490,12 +509,11 @@ bm_status plan_group(bosmusic_s* h, const bosmusic_frame* frames, int i0, int i1
                 float2* gx = (float2*)(h->ws + cur);
                 cur += align_up(px * sizeof(float2), 256);
                 bm::FftJob fj{};
-                if ((st = make_fft_job(h, W, fj)) != BM_OK) return st;
+                if ((st = make_fft_job(h, W, H, fj)) != BM_OK) return st;
                 fj.src = f.data;
                 fj.src_ls = f.row_stride;
                 fj.dst = gx;
                 fj.elem = f.dtype;
-                fj.nlines = H;
                 gp.fft.push_back(fj);
                 gam = gx;
                 gls = W;
@@ -528,12 +546,11 @@ bm_status plan_group(bosmusic_s* h, const bosmusic_frame* frames, int i0, int i1
                 float2* gx = (float2*)(h->ws + cur);
                 cur += align_up(px * sizeof(float2), 256);
                 bm::FftJob fj{};
-                if ((st = make_fft_job(h, W, fj)) != BM_OK) return st;
+                if ((st = make_fft_job(h, W, H, fj)) != BM_OK) return st;
                 fj.src = f.data;
                 fj.src_ls = f.row_stride;
                 fj.dst = gx;
                 fj.elem = f.dtype;
-                fj.nlines = H;
                 gp.fft.push_back(fj);
                 j.gamma = gx;
                 j.gamma_ls = W;
@@ -573,12 +590,11 @@ bm_status plan_group(bosmusic_s* h, const bosmusic_frame* frames, int i0, int i1
                 cur += align_up(px * sizeof(float), 256);
                 tj.dst = tr;
                 bm::FftJob fj{};
-                if ((st = make_fft_job(h, H, fj)) != BM_OK) return st;
+                if ((st = make_fft_job(h, H, W, fj)) != BM_OK) return st;
                 fj.src = tr;
                 fj.src_ls = H;
                 fj.dst = gy;
                 fj.elem = BM_F32;
-                fj.nlines = W;
                 gp.fft.push_back(fj);
             }
             gp.tr.push_back(tj);
@@ -1308,7 +1324,7 @@ void release(bosmusic_s* h) {
     if (h->int_ev) (void)hipEventDestroy(h->int_ev);
     if (h->pin) (void)hipHostFree(h->pin);
     for (auto& kv : h->twiddles) (void)hipFree(kv.second);
-    for (auto& kv : h->bluestein) (void)hipFree(kv.second);
+    for (auto& kv : h->conv) (void)hipFree(kv.second);
     for (auto* v : {&h->ev_free, &h->ev_pending})
         for (auto& e : *v) {
             (void)hipEventDestroy(e.first);
