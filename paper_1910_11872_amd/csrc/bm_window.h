@@ -1397,19 +1397,14 @@ __device__ __forceinline__ bool power_top_eigvec(Sym<L>& T, float hc, float hs, 
     constexpr int o = L - m;
     float v0[L];
     {
-        float er = 1.f, ei = 0.f;
-#pragma unroll
-        for (int k = 0; k < L - 1; ++k) {                  // e^{j w s_0}
-            const float t = er * hc + ei * hs;
-            ei = ei * hc - er * hs;
-            er = t;
-        }
-        const float sr = hc * hc - hs * hs, si = 2.f * hc * hs;
+        // from the middle outwards: e^{j w s_a}, s_{m-1} = -1/2 (even L) or -1, then steps of e^{-j w}
+        const float sr = hc * hc - hs * hs, si = -2.f * hc * hs;
         const float sc = 1.41421356237309515f * frsq((float)L);
+        float er = sc * ((L & 1) ? sr : hc), ei = sc * ((L & 1) ? si : -hs);
 #pragma unroll
-        for (int a = 0; a < m; ++a) {
-            v0[a] = sc * er;
-            v0[o + a] = sc * ei;
+        for (int a = m - 1; a >= 0; --a) {
+            v0[a] = er;
+            v0[o + a] = ei;
             const float t = er * sr - ei * si;
             ei = er * si + ei * sr;
             er = t;
