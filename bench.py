@@ -100,13 +100,24 @@ def certificate_flops(L: int) -> tuple:
 
 def power_route_flops(L: int, steps: float) -> float:
     """The verified power iteration for the signal eigenvector: the start's half-angle
-    (from the lag-1 sums, or the prediction's sincos), the real steering vector, tr T^2,
-    `steps` products T v, the Rayleigh quotient / residual / bound test from the second
-    step on, and the final normalisation."""
+    (from the lag-1 sums, or the prediction's sincos), the real steering vector, tr T^2 and the
+    shift, `steps` products (T - mu I) v, the Rayleigh quotient / residual / bound test from the
+    second step on, and the final normalisation."""
     half = 2 * (L - 1) + 12
-    steer = 6 * (L - 1) + 6 * (L // 2) + 6
-    trace2 = L + 3 * (L * (L - 1) // 2)
-    return half + steer + trace2 + steps * 2 * L * L + max(0.0, steps - 1) * (8 * L + 20) + 3 * L + 2
+    steer = 6 * (L // 2) + 8
+    trace2 = L * (L + 1) + L + 9
+    return half + steer + trace2 + steps * 2 * L * L + max(0.0, steps - 1) * (8 * L + 22) + 3 * L + 2
+
+
+def tone_flops(L: int) -> tuple:
+    """(FP64, FP32) flops of the closed-form pair of a window close to one tone: the guess from
+    the signal vector's lag-1 sum, the normalised direction and the L/2 rotated terms in FP64,
+    the step to the peak, the terms rotated by it, six moments and the pair from them (the
+    arctangent counts as one)."""
+    m = L // 2
+    fp64 = 7 + (0 if L & 1 else 5) + 6 * m + 6 * (m - 1)
+    fp32 = 8 * (m - 1) + 18 + 6 + 5 * m + 2 + 20 + 6 * m + 6 * (m - 1) + 11 * m + 46
+    return fp64, fp32
 
 
 def flops_per_window(L: int, N: int, newton: float, iters: float, pair_iters: float = 0.0,
@@ -116,12 +127,14 @@ def flops_per_window(L: int, N: int, newton: float, iters: float, pair_iters: fl
 
     FMA = 2 flops; add, sub, mul, rcp, sqrt, rsq = 1 each.  `newton` is the
     measured mean number of Newton steps for the largest eigenvalue per
-    window, `pair_iters32` and `pair_iters` the mean FP32 and FP64 Newton
-    steps for the signal root before the certificate, `cert_frac` the fraction of windows
-    finished by the certificate, and `iters` the mean simultaneous root
+    window, `pair_iters32` and `pair_iters` the mean FP32 and FP64 steps for the signal root
+    (one each for the closed form of a window close to one tone, which every window tries; the
+    rest are Newton steps of the windows it does not serve, of which at most
+    `pair_iters` - 1 per window can have taken one or more), `cert_frac` the fraction of windows
+    finished by one pair, and `iters` the mean simultaneous root
     iterations of the windows whose roots were all found.  Certificate work
     of a window that fails it is not counted.  `block`: the L x L block
-    window, whose covariance is summed directly from its L snapshots.  `quad_lags`: the line
+    window, whose lag sums are shared by the windows of a 16 x 16 tile.  `quad_lags`: the line
     kernel's lane-pair lag sums of four starts for L >= 7 (the surrogate kernel keeps two starts
     per lane).
     The eigenvalue Newton steps cost 8L flops each (the characteristic
@@ -132,9 +145,11 @@ def flops_per_window(L: int, N: int, newton: float, iters: float, pair_iters: fl
     K = N - L + 1
     n = 2 * L - 2
     if block:
-        # block window: T summed straight from the L snapshots, a_k + j b_k = sqrt2 Q^H s_k
-        # (2 L adds) and the upper triangle of a a^T + b b^T (two FMAs per entry)
-        lag = L * (2 * L + 4 * (L * (L + 1) // 2))
+        # block window: lag d of a tile has 16 + L - 1 - d rows of 16 sums of L products, formed
+        # C at a time from L + C - 1 products (4 FMA each) and C - 1 complex additions; then T
+        C = 8 if L >= 8 else 4 if L >= 4 else 2
+        lag = sum((15 + L - d) * (16 // C) * ((L + C - 1) * 8 + (C - 1) * 2) for d in range(L)) / 256
+        lag += 4 * (L // 2) * (L // 2 + 1) + (4 * (L // 2) + 1 if L & 1 else 0)
     elif L >= 7 and quad_lags:
         # lag sums (complex MAC = 4 FMA; the zero lag is real, 2 FMA): a lane pair sums the
         # first of four starts directly (K L MACs) and slides to the next three (2 L MACs each)
@@ -149,19 +164,26 @@ def flops_per_window(L: int, N: int, newton: float, iters: float, pair_iters: fl
     inverse = 6 * L + 2 * 8 * L + sum(4 * l for l in range(2, L))
     eigen = (1.0 - power_frac) * (house + newton_f + inverse) + power_frac * power_route_flops(L, power_steps)
     coef = 2 * L + 8 * L * (L + 1) // 2
-    # start of the signal-root Newton: two evaluations of the real spectral function g, g', g''
-    # (half-angle powers and the L/2 terms), the peak step, the half-angle and the radius
+    # the closed form, tried by every window unless every root is asked for
+    tried = 1.0 if pair_iters > 0.0 else 0.0
+    tone64, tone32 = tone_flops(L)
+    rest = min(1.0, max(0.0, pair_iters - 1.0)) if tried else 1.0      # windows it does not serve, at most
+    # their start of the signal-root Newton: two evaluations of the real spectral function g, g',
+    # g'' (half-angle powers and the L/2 terms), the peak step, the half-angle and the radius
     spectral_start = 2 * (6 * (L - 1) + 9 * L + 5) + 25
-    common32 = lag + build_t + eigen + coef + 20 + spectral_start
+    common32 = lag + build_t + eigen + tried * tone32 + rest * (coef + 20 + tried * spectral_start)
     full = 1.0 - cert_frac
+    certified = max(0.0, cert_frac - (1.0 - rest))
     start = 4 * n + 40
     aberth = iters * (n * (30 + 16 * n) + 12 * n * (n - 1) // 2 + 27 * n)
     select = 11 * n
     cert64, cert32 = certificate_flops(L)
+    steps32, steps64 = max(0.0, pair_iters32 - tried), max(0.0, pair_iters - tried)
     # the FP64 Newton stage: P and P' in FP64, the corrected step from them in FP32 (~62 flops)
-    fp32 = (common32 + full * (start + aberth + select) + pair_iters32 * pair_newton_flops(L) + cert_frac * cert32
-            + pair_iters * 62)
-    fp64 = pair_iters * (pair_newton_flops(L) - 62) + cert_frac * cert64 + full * 3 * bairstow_flops(n)
+    fp32 = (common32 + full * (start + aberth + select) + steps32 * pair_newton_flops(L) + certified * cert32
+            + steps64 * 62)
+    fp64 = (tried * tone64 + steps64 * (pair_newton_flops(L) - 62) + certified * cert64
+            + full * 3 * bairstow_flops(n))
     return {"fp32": fp32, "fp64": fp64, "total": fp32 + fp64}
 
 
@@ -336,7 +358,7 @@ def workload(name, nframes):
         fr = [wl.exp_frame(i) for i in range(nframes or 19)]
         desc = (f"{len(fr)} time-lapsed 1850x700 8-bit frames (stand-in for the paper's experimental diffusion "
                 f"series), carrier 0.11 cyc/px at 35 deg, 5*erf phase, SNR 12 dB; x and y windows N=15, L=7; "
-                f"analytic step through Bluestein's identity (neither length is 5-smooth); "
+                f"rows as one circular convolution (1850 = 2 * 5^2 * 37); "
                 f"plain root-MUSIC + FP64 phase integration")
     else:
         raise SystemExit(f"unknown workload {name}")
@@ -682,7 +704,7 @@ def main():
         "data": "synthetic",
         "config": {"workload": desc, "name": args.workload, "frames": nf, "pixels": total_px,
                    "dirs": "xy", "mode": modes[0], "modes": modes, "graph": use_graph, "warm_start": args.warm,
-                   "roots": "all" if args.full_roots else "certified pair, all roots where uncertified",
+                   "roots": "all" if args.full_roots else "one proven pair, all roots where unproven",
                    **({"predictor": args.predictor} if "surrogate" in modes else {})},
         "roofline": first["roofline"],
         "cpu_baseline": cpu,

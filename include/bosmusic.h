@@ -25,7 +25,9 @@
  *     phase, or at the surrogate's prediction);
  *   - root-MUSIC polynomial a(z)^H Un Un^H a(z) (Eq. 12) from the diagonal
  *     sums of the noise projector, degree 2L-2;
- *   - the root pair nearest the unit circle (Sec. 3, selection rule): found
+ *   - the root pair nearest the unit circle (Sec. 3, selection rule): in
+ *     closed form where the signal vector is close enough to one tone's to
+ *     prove that it is the only pair near the circle; else found
  *     alone by Newton's method for the signal root and proven nearest by a
  *     root-count certificate, or, where that proof fails (or with
  *     BM_OPT_FULL_ROOTS), selected from all 2L-2 roots; omega = arg of the
@@ -147,10 +149,10 @@ typedef struct {
      * the previous frame of a time-lapsed series, the same size, row stride =
      * width (the paper's premise that the phase changes little between
      * successive frames, Sec. 1 and 4).  Where the previous frequency at the
-     * pixel is finite, the Newton iteration for the window's signal root
+     * pixel is finite, the search for the window's signal root
      * starts in its direction instead of the window's own lag-1 direction.
-     * The certified pair, hence omega, is the same either way (up to
-     * rounding); only the iteration counts change.  NULL: no warm start. */
+     * The pair, hence omega, is the same either way (up to
+     * rounding); only the steps to it change.  NULL: no warm start. */
     const float* prev_omega_x;
     const float* prev_omega_y;
 } bosmusic_frame;
@@ -167,14 +169,16 @@ typedef struct {
     uint64_t sur_accepted;  /* BM_SURROGATE: windows whose signal eigenvector came from the
                                prediction (proven converged, null spectrum at the
                                prediction <= tau);
-                               BM_PLAIN: windows finished by the certified pair */
+                               BM_PLAIN: windows finished by one proven pair */
     uint64_t sur_rejected;  /* BM_SURROGATE: windows finished by the plain eigen-split;
                                BM_PLAIN: windows whose roots were all found */
-    uint64_t pair_iters;    /* sum over windows of FP64 Newton steps for the signal root
-                               (its mate divided out) before the certificate */
+    uint64_t pair_iters;    /* sum over windows of FP64 steps for the signal root: one for the
+                               closed form that every window tries, and the Newton steps (its
+                               mate divided out) of the windows it does not serve; 0 with
+                               BM_OPT_FULL_ROOTS */
     uint64_t rm_launches;   /* root-MUSIC kernel launches timed (BM_OPT_TIMING) */
     uint64_t rm_time_ns;    /* their summed duration between HIP events, ns */
-    uint64_t pair_iters32;  /* sum over windows of FP32 Newton steps for the signal root,
+    uint64_t pair_iters32;  /* the same for FP32 steps: one per window, and the Newton steps
                                taken before the FP64 ones */
     uint64_t power_windows; /* windows whose signal eigenvector came from the verified power
                                iteration (the rest took the tridiagonal solver); eig_iters
@@ -252,7 +256,7 @@ bm_status bosmusic_get_stats(bosmusic_t h, bosmusic_stats* out, int32_t reset, v
  * a-posteriori bound proves it within 1e-5 rad of the top eigenvector and
  * the MUSIC null spectrum 1 - |u1^H a(w_hat)|^2 / L at the prediction is at
  * most tau.  Any other window takes the plain eigen-split.  From u1 on every
- * window follows the plain path (polynomial, Eq. 12-14; certified pair or
+ * window follows the plain path (polynomial, Eq. 12-14; the proven pair or
  * all roots; w = arg(z1 + z2), Eq. 15), so the output equals the plain
  * output up to the eigenvector bound and rounding.  Line windows with
  * L <= 8 and N >= 16 only.

@@ -1,11 +1,11 @@
 // Per-window root-MUSIC local-frequency kernels for gfx950 (device code and
 // launch templates, shared by bm_rootmusic.hip and bm_bigblock.hip).
 //
-// One lane owns one window (one output pixel of one direction).  A block of
-// BLOCK lanes (128 or 256) covers BLOCK-(L-1) consecutive window positions of one line; the
+// One lane owns two windows (two output pixels of one direction).  A block of
+// BLOCK lanes (128 or 256) covers 2 BLOCK - (L-1) consecutive window starts of one line; the
 // overlapping windows are staged once in LDS with coalesced loads.  Steps:
 //
-//   lag sums    S_d(m) = sum_k g[m+k] conj(g[m+k+d]), d < L, one start m per
+//   lag sums    S_d(m) = sum_k g[m+k] conj(g[m+k+d]), d < L, two starts m per
 //               lane, shared through LDS: the covariance of the window that
 //               starts at s is R_ij = S_{j-i}(s+i)             (paper Eq. 4)
 //   FB average + unitary real transform: T = Q^H R_fb Q is real symmetric
@@ -13,7 +13,8 @@
 //               closed form from R without forming R_fb
 //   eigen-split the eigenvector v of the largest eigenvalue of T gives the
 //               signal subspace u1 = Q v (paper Eq. 6-11, one-dimensional
-//               signal subspace).  Power iteration on T from
+//               signal subspace).  Power iteration on T, shifted by the
+//               mean of its other eigenvalues, from
 //               the steering vector of the window's lag-1 phase, kept when
 //               an a-posteriori bound proves it within 1e-5 rad of the top
 //               eigenvector (2-3 steps at 10 dB).  Otherwise: Householder
@@ -23,11 +24,16 @@
 //               eigenvalue, one shifted inverse iteration for its
 //               eigenvector, back-transformation.  The cyclic Jacobi solver
 //               is kept as a selectable alternative.
+//   closed-form pair  a window whose u1 is close to one tone's steering
+//               vector has, by Rouche's theorem, one root pair near the
+//               circle, and the derivatives of the spectrum at its peak give
+//               that pair (tone_omega): nearly every window ends here.  The
+//               steps below serve the others.
 //   polynomial  c_k = sum_i C[i,i+k] with C = I - u1 u1^H = Un Un^H
 //               (paper Eq. 12-14)
-//   certified pair  FP64 Newton for the signal root with its mate
+//   certified pair  Newton (FP32, then FP64) for the signal root with its mate
 //               1/conj(z) divided out, started just inside the unit circle
-//               at the phase of c_1; accepted when the polynomial divides by
+//               at the peak of the spectrum; accepted when the polynomial divides by
 //               the pair's factor and a Schur-Cohn count on the quotient
 //               puts every other inner root strictly inside |z_in|: that
 //               pair is the one the selection below would pick.  Windows

@@ -5,7 +5,7 @@
 // lane, lag sums shared through LDS), with a cheaper route to the signal
 // subspace where the network's estimate allows it:
 //   1. stage the analytic signal of the block in LDS;
-//   2. features of every 8th window: 16 central samples, de-rotated by the
+//   2. features of every 32nd window: 16 central samples, de-rotated by the
 //      phase of the central sample, divided by the window's RMS magnitude, as
 //      bfloat16 [Re(16), Im(16)];
 //   3. MLP 32 -> GELU 64 -> GELU 64 -> 2 on the matrix cores: every GEMM is
@@ -19,8 +19,8 @@
 //      within 1e-5 of the eigenvector and the MUSIC null spectrum at
 //      omega_hat is below tau; otherwise the plain eigen-split (Householder,
 //      Newton, inverse iteration);
-//   5. the plain path's polynomial, certified root pair (or all roots) and
-//      omega = arg(z1 + z2) either way.
+//   5. the plain path's root pair (closed form, certified, or from all roots)
+//      and omega = arg(z1 + z2) either way.
 // A better prediction needs fewer power steps; a window the prediction does
 // not serve is computed by the plain path in the same lane.
 #include "bm_rootmusic_kernels.h"

@@ -950,6 +950,8 @@ __device__ __forceinline__ bool tone_omega(const float (&v)[L], float cw, float 
     constexpr bool odd = (L & 1) != 0;
     constexpr float kSqrt2 = 1.41421356237309515f;
     constexpr float kmax = 0.5f * (float)(L - 1);
+    // |tau| <= sqrt(0.2) / kmax (below) keeps the pair inside the annulus: e^{-|tau|} >= 1 - |tau| > kappa
+    static_assert(L < 3 || 1.f - 0.4473f / kmax > tone_kappa(L), "the pair lies inside the annulus of the argument above");
     // e^{j w} (odd L) or e^{j w/2} (even L, cos(w/2) >= 0), normalised in FP64
     float fr = cw, fi = sw;
     if (!odd) {
