@@ -15,8 +15,8 @@
 // What bounds it: VALU issue, with the LDS reads of the lag sums (L (L+1)/2
 // per window and direction) beside it at about half their rate's limit.
 // Measured against summing each window's T from its own snapshots, on 20
-// frames of 1024 x 1024 with 11 x 11 blocks 4.25 -> 1.82 ms, one 1850 x 700
-// frame with 15 x 15 blocks and the phase 0.96 -> 0.31 (all the call's launches).
+// frames of 1024 x 1024 with 11 x 11 blocks 4.25 -> 1.74 ms, one 1850 x 700
+// frame with 15 x 15 blocks and the phase 0.96 -> 0.29 (all the call's launches).
 // The
 // eigen-split's real symmetric T holds L (L+1)/2 registers, so the sizes above
 // 8 x 8 keep only the common route in this kernel (power iteration, then the
@@ -380,7 +380,15 @@ void block_tile_kernel(RmBatch B) {
 // for one as for 64 (4 x 1024^2 at 3 dB, 9 x 9 blocks: 1.51 ms with the windows
 // left on their own lanes, 0.88 gathered; where nothing is left, reading the
 // maps for it instead of the bytes cost 0.34 ms of 1.16 per 10 x 1024^2).
-constexpr int kRestTiles = 4;
+// Where few windows are left, what a block costs is the latency of one pass
+// (reads of the maps, gathering, one wave's worth of every solver), so a pass
+// takes up to kRestTiles tiles, looks their places up once and reads the maps
+// of kRestScan tiles together: against four tiles a pass, each looked up and
+// read in turn, 20 x 1024^2 at 10 dB with 9 x 9 blocks 1.57 -> 1.46 ms, 11 x 11
+// 1.80 -> 1.75, 4 x 1024^2 at 3 dB 0.97 -> 0.94, one 1850 x 700 frame 164 -> 157 us.
+constexpr int kRestTiles = 16;
+constexpr int kRestScan = 4;           // marked tiles whose maps are read together
+constexpr int kRestChunk = 4;          // neighbouring tiles of a block's chunk
 constexpr unsigned kListed = 0x80u, kNoPower = 0x40u;
 
 template <int L, bool STATS>
@@ -389,6 +397,7 @@ __global__ __launch_bounds__(kTileLanes) void block_rest_kernel(RmBatch B, int c
     __shared__ unsigned short list[2 * kRestTiles * kTileLanes];   // slot << 9 | direction << 8 | pixel
     __shared__ unsigned char flag[2 * kRestTiles * kTileLanes];    // by the same index: BM_FLAG_*, kListed
     __shared__ int tiles[kTileLanes];                              // work items of the marked tiles
+    __shared__ int tjob[kRestTiles], tline[kRestTiles], tpix[kRestTiles];   // job, first line and pixel of a listed tile
     __shared__ int ntiles, count;
     LaneStats ls;
     const int t = threadIdx.x;
@@ -398,59 +407,81 @@ __global__ __launch_bounds__(kTileLanes) void block_rest_kernel(RmBatch B, int c
     const int64_t w = ((int64_t)(t / chunk) * gridDim.x + blockIdx.x) * chunk + t % chunk;
     if (w < B.total && (B.full_roots || B.left[w])) tiles[atomicAdd(&ntiles, 1)] = (int)w;
     __syncthreads();
-    // pixel q of work item w
-    auto place = [&](int w, int q, int& j, int& line, int& p) {
-        j = find_job(B.prefix, B.njobs, w);
-        const RmJob& J = B.jobs[j];
-        const int local = w - B.prefix[j];
-        const int tr = local / J.bpl;
-        line = tr * kTile + (q >> 4);
-        p = (local - tr * J.bpl) * kTile + (q & 15);
-        return line < J.nlines && p < J.len;
+    // pixel q of listed tile k
+    auto place = [&](int k, int q, int& line, int& p) {
+        line = tline[k] + (q >> 4);
+        p = tpix[k] + (q & 15);
     };
     const int nt = ntiles;
     for (int b0 = 0; b0 < nt; b0 += kRestTiles) {
+        const int n_tiles = nt - b0 < kRestTiles ? nt - b0 : kRestTiles;
         if (t == 0) count = 0;
+        if (t < n_tiles) {
+            const int item = tiles[b0 + t], j = find_job(B.prefix, B.njobs, item);
+            const int local = item - B.prefix[j], tr = local / B.jobs[j].bpl;
+            tjob[t] = j;
+            tline[t] = tr * kTile;
+            tpix[t] = (local - tr * B.jobs[j].bpl) * kTile;
+        }
         __syncthreads();
-        for (int k = 0; k < kRestTiles && b0 + k < nt; ++k) {
-            int j, line, p;
-            if (!place(tiles[b0 + k], t, j, line, p)) continue;
-            const RmJob& J = B.jobs[j];
-            const int64_t o = (int64_t)p * J.out_es + (int64_t)line * J.out_ls;
-            const bool valid = line >= h && line - h + L <= J.nlines && p >= h && p - h + L <= J.len;
-            for (int dir = 0; dir < 2; ++dir) {
-                const int e = k << 9 | dir << 8 | t;
-                flag[e] = 0;
-                if (!(J.bdirs & (dir == 0 ? BM_DIR_X : BM_DIR_Y))) continue;
-                float* out = (dir == 0 ? J.out : J.out_y) + o;
-                if (B.full_roots) {
-                    // nothing ran before: borders are written here
-                    if (!valid) {
-                        *out = __builtin_nanf("");
-                        flag[e] = BM_FLAG_UNDEFINED;
+        for (int k0 = 0; k0 < n_tiles; k0 += kRestScan) {
+            float w2[kRestScan][2];
+#pragma unroll
+            for (int u = 0; u < kRestScan; ++u) {
+                w2[u][0] = w2[u][1] = 0.f;
+                int line, p;
+                if (B.full_roots || k0 + u >= n_tiles) continue;
+                place(k0 + u, t, line, p);
+                const RmJob& J = B.jobs[tjob[k0 + u]];
+                if (line >= J.nlines || p >= J.len) continue;
+                const int64_t o = (int64_t)p * J.out_es + (int64_t)line * J.out_ls;
+                if (J.bdirs & BM_DIR_X) w2[u][0] = J.out[o];
+                if (J.bdirs & BM_DIR_Y) w2[u][1] = J.out_y[o];
+            }
+#pragma unroll
+            for (int u = 0; u < kRestScan; ++u) {
+                const int k = k0 + u;
+                int line, p;
+                if (k >= n_tiles) continue;
+                place(k, t, line, p);
+                const RmJob& J = B.jobs[tjob[k]];
+                if (line >= J.nlines || p >= J.len) continue;
+                const int64_t o = (int64_t)p * J.out_es + (int64_t)line * J.out_ls;
+                const bool valid = line >= h && line - h + L <= J.nlines && p >= h && p - h + L <= J.len;
+#pragma unroll
+                for (int dir = 0; dir < 2; ++dir) {
+                    const int e = k << 9 | dir << 8 | t;
+                    flag[e] = 0;
+                    if (!(J.bdirs & (dir == 0 ? BM_DIR_X : BM_DIR_Y))) continue;
+                    if (B.full_roots) {
+                        // nothing ran before: borders are written here
+                        if (!valid) {
+                            (dir == 0 ? J.out : J.out_y)[o] = __builtin_nanf("");
+                            flag[e] = BM_FLAG_UNDEFINED;
+                            continue;
+                        }
+                    } else if (!pending(w2[u][dir])) {
                         continue;
                     }
-                } else if (!pending(*out)) {
-                    continue;
+                    const bool tried = !B.full_roots && __float_as_uint(w2[u][dir]) == kPendingEig;
+                    flag[e] = (unsigned char)(kListed | (tried ? kNoPower : 0u));
+                    list[atomicAdd(&count, 1)] = (unsigned short)e;
                 }
-                const bool tried = !B.full_roots && __float_as_uint(*out) == kPendingEig;
-                flag[e] = (unsigned char)(kListed | (tried ? kNoPower : 0u));
-                list[atomicAdd(&count, 1)] = (unsigned short)e;
-            }
-            if (B.full_roots && !valid) {
-                if (J.phase) J.phase[o] = __builtin_nanf("");
-                if (J.flags)
-                    J.flags[(int64_t)p * J.flag_es + (int64_t)line * J.flag_ls] =
-                        (uint8_t)(flag[k << 9 | t] | flag[k << 9 | 256 | t] << 4);
+                if (B.full_roots && !valid) {
+                    if (J.phase) J.phase[o] = __builtin_nanf("");
+                    if (J.flags)
+                        J.flags[(int64_t)p * J.flag_es + (int64_t)line * J.flag_ls] =
+                            (uint8_t)(flag[k << 9 | t] | flag[k << 9 | 256 | t] << 4);
+                }
             }
         }
         __syncthreads();
         const int n = count;
         for (int i = t; i < n; i += kTileLanes) {
             const int e = list[i], dir = (e >> 8) & 1;
-            int j, line, p;
-            place(tiles[b0 + (e >> 9)], e & 255, j, line, p);
-            const RmJob& J = B.jobs[j];
+            int line, p;
+            place(e >> 9, e & 255, line, p);
+            const RmJob& J = B.jobs[tjob[e >> 9]];
             const float2* g = J.gamma + (int64_t)(line - h) * J.gamma_ls + (p - h);
             const int64_t sk = dir == 0 ? J.gamma_ls : 1, si = dir == 0 ? 1 : J.gamma_ls;   // s_k[i] = g[k sk + i si]
             float omega = __builtin_nanf("");
@@ -483,9 +514,9 @@ __global__ __launch_bounds__(kTileLanes) void block_rest_kernel(RmBatch B, int c
         // entry's, or its omega_y entry's when omega_x was not on the list
         for (int i = t; i < n; i += kTileLanes) {
             const int e = list[i];
-            int j, line, p;
-            place(tiles[b0 + (e >> 9)], e & 255, j, line, p);
-            const RmJob& J = B.jobs[j];
+            int line, p;
+            place(e >> 9, e & 255, line, p);
+            const RmJob& J = B.jobs[tjob[e >> 9]];
             if ((e & 256) && (flag[e ^ 256] & kListed)) continue;
             if (J.flags) {
                 uint8_t* f = J.flags + (int64_t)p * J.flag_es + (int64_t)line * J.flag_ls;
@@ -562,10 +593,10 @@ hipError_t launch_big_block(const RmBatch& b, hipStream_t s) {
         const hipError_t e = launch_block_LJ<L, false>(b, s);
         if (e != hipSuccess) return e;
     }
-    // kRestTiles tiles per block for dense lists, one while there are few tiles (spread over
+    // kRestChunk tiles per block for dense lists, one while there are few tiles (spread over
     // the CUs), and several chunks of them (strided) above 8192 tiles, so that tiles without
     // anything left cost few blocks; a block looks at kTileLanes tiles at most
-    const int chunk = b.total <= 1024 ? 1 : kRestTiles;
+    const int chunk = b.total <= 1024 ? 1 : kRestChunk;
     const int chunks = (b.total + chunk - 1) / chunk, most = kTileLanes / chunk;
     const int g = chunks < 2048 ? chunks : 2048, least = (chunks + most - 1) / most;
     const dim3 grid(g > least ? g : least);

@@ -59,3 +59,24 @@ def test_pending_windows_agree_with_all_roots(bm, L, W, H):
     assert np.array_equal(m, np.isfinite(a[3]))
     d = np.abs((a[3][m] - b[3][m] + np.pi) % (2 * np.pi) - np.pi)
     assert np.quantile(d, 0.999) <= 1e-3
+
+
+@pytest.mark.parametrize("L,frames", [(9, 20), (11, 18)])
+def test_blocks_with_many_left_tiles(bm, L, frames):
+    """-6 dB: nearly every tile has windows left; each half of the batch holds more than 16 of them
+    per block, a single frame four.  The same windows by the same arithmetic, bit for bit."""
+    import torch
+    W = H = 1024
+    img = torch.from_numpy(wl.random_frame(W, H, seed=L, snr_db=-6.0).astype(np.float32)).cuda()
+    both = bm.BM_DIR_X | bm.BM_DIR_Y | bm.BM_BLOCK
+    dem = bm.Demodulator(0, max_width=W, max_height=H, max_batch_pixels=frames * W * H)
+    out = torch.empty((2, frames + 1, H, W), device="cuda")
+    fl = torch.empty((frames + 1, H, W), dtype=torch.uint8, device="cuda")
+    specs = [bm.FrameSpec(img, L, L, both, out[0, t], out[1, t], flags=fl[t]) for t in range(frames + 1)]
+    bm.bosmusic_demodulate(dem.h, specs[:frames])
+    bm.bosmusic_demodulate(dem.h, specs[frames:])
+    torch.cuda.synchronize()
+    dem.close()
+    bits = out.view(torch.int32)
+    for t in range(frames):
+        assert torch.equal(bits[:, t], bits[:, frames]) and torch.equal(fl[t], fl[frames]), t
