@@ -426,6 +426,17 @@ bm_status validate_frame(bosmusic_s* h, const bosmusic_frame& f, int idx) {
     return BM_OK;
 }
 
+// Pixels times directions of a group from which its two halves run on two
+// streams.  The split hides the second half's transposes and analytic step
+// behind the first half's root-MUSIC launch, and costs a second set of
+// launches, four events and the drained chip at the end of each half's launch.
+// One launch against two halves: 2 x 256^2 34 against 93 us, 2 x 1024^2 140
+// against 180, 20 x 1024^2 with 11 x 11 blocks 1.65 against 1.80 ms, 32 x
+// 1024^2 1.78 against 1.85; 12 x 2048^2 (L = 4) 2.05 against 1.97, 100 x
+// 1024^2 5.67 against 5.50, 16 x 4096^2 16.90 against 16.79.  Line windows
+// break even at about 80 M, block windows at 130 M.
+constexpr int64_t kSplitWork = 96000000;
+
 size_t frame_ws_bytes(const bosmusic_frame& f) {
     const size_t px = (size_t)f.width * (size_t)f.height;
     if (f.dirs & BM_BLOCK)
@@ -1493,7 +1504,11 @@ bm_status bosmusic_demodulate(bosmusic_t h, const bosmusic_frame* frames, int32_
         const bool graph = (h->options & BM_OPT_GRAPH) && !(h->options & BM_OPT_TIMING);
         if (graph) return run_graph(h, frames, n_frames, groups, mode, s);
         for (auto& g : groups) {
-            if (g.second - g.first >= 2 && !(h->options & BM_OPT_TIMING)) {
+            int64_t work = 0;
+            for (int i = g.first; i < g.second; ++i)
+                work += (int64_t)frames[i].width * frames[i].height *
+                        (((frames[i].dirs & BM_DIR_X) != 0) + ((frames[i].dirs & BM_DIR_Y) != 0));
+            if (g.second - g.first >= 2 && work >= kSplitWork && !(h->options & BM_OPT_TIMING)) {
                 // two halves pipelined on two streams (results do not depend on the split);
                 // with BM_OPT_TIMING each root-MUSIC launch runs alone, timed by its events
                 const int mid = g.first + (g.second - g.first + 1) / 2;

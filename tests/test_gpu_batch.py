@@ -259,3 +259,32 @@ def test_cfg3_full_batch_one_graph_replay_sampled(bm, torch):
         compare_omega(gx[rows], oracle_rows(f.data, rows, f.L, f.N), f"cfg3 graph k{k} x")
         compare_omega(gy[:, cols].T, oracle_cols(f.data, cols, f.L, f.N), f"cfg3 graph k{k} y")
     d.close()
+
+
+@pytest.mark.parametrize("frames,dirs", [(45, 3), (46, 3), (92, 2)])
+def test_large_batches_under_and_over_the_split(bm, torch, frames, dirs):
+    """Just under and over the size from which a batch runs as two halves on two streams: on a side
+    stream, poisoned outputs and back-to-back calls, bit for bit the frame alone."""
+    W = H = 1024
+    assert (frames * W * H * bin(dirs).count("1") >= 96_000_000) == (frames > 45)
+    imgs = [torch.from_numpy(wl.random_frame(W, H, seed=60 + k).astype(np.float32)).cuda() for k in range(3)]
+    d = bm.Demodulator(0, max_width=W, max_height=H, max_batch_pixels=frames * W * H)
+    out = torch.empty((2, frames, H, W), device="cuda")
+    maps = lambda t: [out[k, t] if dirs >> k & 1 else None for k in range(2)]
+    specs = [bm.FrameSpec(imgs[t % 3], 3, 8, dirs, *maps(t)) for t in range(frames)]
+    for s in specs[:3]:
+        bm.bosmusic_demodulate(d.h, [s])
+    torch.cuda.synchronize()
+    ref = out[:, :3].clone().view(torch.int32)
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        for rep in range(2):
+            out.fill_(123.0 + rep)
+            bm.bosmusic_demodulate(d.h, specs, stream=side)
+        snap = out.clone().view(torch.int32)
+    side.synchronize()
+    for t in range(frames):
+        for k in range(2):
+            if dirs >> k & 1:
+                assert torch.equal(snap[k, t], ref[k, t % 3]), (t, k)
+    d.close()
