@@ -45,12 +45,12 @@ PEAK_FP32_VECTOR = 157.3e12      # MI355X published FP32 vector peak (packed), F
 NEWTON_STEPS_TRIDIAG = 2.11
 PEAK_HBM = 8.0e12
 # HBM bytes per pixel and direction of the line-window root-MUSIC launch (L=8, N=32, FP16 4096x4096
-# frames): FETCH_SIZE x 2.0 + WRITE_SIZE x 1.0 from rocprofv3 --pmc on two cfg4 frames
-# (profiles/rootmusic_surrogate_cfg4_counters.md).  Valid only for that kernel and configuration;
+# frames): FETCH_SIZE x 2.0 + WRITE_SIZE x 1.0 from rocprofv3 --pmc on a launch of eight such frames
+# (profiles/case_counters.md).  Valid only for that kernel and configuration;
 # the other configurations report null.
-TRAFFIC_BYTES_PER_PIXEL_DIR_CFG4 = (287208.0 * 2.0 + 262144.0) * 1024 / (2 * 2 * 4096 * 4096)
-# The same for the surrogate kernel on those frames (same profile).
-TRAFFIC_BYTES_PER_PIXEL_DIR_CFG4_SURROGATE = (287417.0 * 2.0 + 262144.0) * 1024 / (2 * 2 * 4096 * 4096)
+TRAFFIC_BYTES_PER_PIXEL_DIR_CFG4 = (1146990.0 * 2.0 + 1048576.0) * 1024 / (2 * 8 * 4096 * 4096)
+# The same for the surrogate kernel on a launch of two.
+TRAFFIC_BYTES_PER_PIXEL_DIR_CFG4_SURROGATE = (287081.0 * 2.0 + 262144.0) * 1024 / (2 * 2 * 4096 * 4096)
 
 
 def bairstow_flops(n: int) -> int:
