@@ -884,6 +884,17 @@ constexpr float tone_kappa(int L) {
          : L == 9 ? 0.70f : L <= 11 ? 0.75f : L <= 13 ? 0.78f : L <= 15 ? 0.81f : 0.83f;
 }
 
+// e^{j w/2} = (hc, hs), hc >= 0, from e^{j w} = (cw, sw).  The larger of the two from the
+// square root, the other from sin w = 2 sin(w/2) cos(w/2): with sqrt((1 + cw) / 2) for hc
+// everywhere, cw's rounding made |(hc, hs)|^2 off by up to 3% within 5e-3 rad of +-pi, which
+// one step of normalisation does not mend (tone_omega was off by up to 5e-5 rad there).
+__device__ __forceinline__ void half_direction(float cw, float sw, float& hc, float& hs) {
+    const float big = fsqrt(fmaf(0.5f, fabsf(cw), 0.5f));
+    const float small = 0.5f * fabsf(sw) * frcp(big);
+    hc = cw < 0.f ? small : big;
+    hs = copysignf(cw < 0.f ? big : small, sw);
+}
+
 // Direction of the frequency guess from the lag-1 coefficient: u1[i+1]/u1[i]
 // ~ e^{j w}, so S = sum_i u1[i] conj(u1[i+1]) = -c_1 ~ e^{-j w} and e^{j w} =
 // conj(S) / |S| (no trigonometric functions needed); (1, 0) when S vanishes.
@@ -929,10 +940,12 @@ __device__ __forceinline__ void guess_direction(const float (&v)[L], float& cw, 
 // Only the angles k_i w need more than FP32: an error of theirs is an error of
 // omega, so e^{j k w} comes from FP64 products of the normalised guess and x
 // and y are formed in FP64 (FP32 leaves 1e-7 rad of the recurrence's rounding);
-// everything after is relative to the small a, x and T.  In numpy trials (L =
-// 2-8, 3-60 dB, FP32 where this code has it) omega is within 1e-9 rad of the
-// FP64 root at the 99.9th percentile, where Newton's iteration on P in FP64
-// stopped within 1e-8.  T below zero is a pair on the circle, which FP32
+// everything after is relative to the small a, x and T.  This code on the host
+// (L = 2-8, 8-30 dB, frequencies up to +-pi) has w + a + x within 2e-9 rad of
+// the FP64 root of the same vector at the 99.9th percentile, 9e-9 at 3 dB and
+// for guesses 0.03 rad off (Newton's iteration on P in FP64 stopped within
+// 1e-8); forming omega from them in FP32 adds its rounding, 1.2e-7 between 1
+// and 2 and twice that above.  T below zero is a pair on the circle, which FP32
 // rounding of |v| makes of a double root there: the same formula gives the
 // mean angle of the two.  False (nothing written) when the window is not within
 // tone_s2 of a tone, the step to the peak is not small, the peak is not
@@ -954,11 +967,7 @@ __device__ __forceinline__ bool tone_omega(const float (&v)[L], float cw, float 
     static_assert(L < 3 || 1.f - 0.4473f / kmax > tone_kappa(L), "the pair lies inside the annulus of the argument above");
     // e^{j w} (odd L) or e^{j w/2} (even L, cos(w/2) >= 0), normalised in FP64
     float fr = cw, fi = sw;
-    if (!odd) {
-        fr = fsqrt(fmaxf(0.5f * (1.f + cw), 0.f));
-        fi = fr > 1e-3f ? 0.5f * sw * frcp(fr) : 1.f;
-        if (!(fr > 1e-3f)) fr = 0.f;
-    }
+    if (!odd) half_direction(cw, sw, fr, fi);
     double br = (double)fr, bi = (double)fi;
     const double nm = fma(-0.5, fma(br, br, bi * bi), 1.5);     // 1/|b| for |b|^2 = 1 + O(1e-6)
     br *= nm;
@@ -1513,9 +1522,7 @@ __device__ __forceinline__ void half_angle_of(float sr, float si, float& hc, flo
     const bool ok = m2 > 0.f && finitef(m2);
     const float im = ok ? frsq(m2) : 0.f;
     const float cw = ok ? sr * im : 1.f, sw = ok ? si * im : 0.f;
-    hc = fsqrt(fmaxf(0.5f * (1.f + cw), 0.f));
-    hs = hc > 1e-3f ? 0.5f * sw * frcp(hc) : 1.f;
-    if (!(hc > 1e-3f)) hc = 0.f;
+    half_direction(cw, sw, hc, hs);
 }
 
 template <int L>

@@ -1,0 +1,100 @@
+"""The kernels' per-window arithmetic (bm_window.h), compiled for the host, against FP64."""
+import ctypes
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
+
+
+@pytest.fixture(scope="module")
+def host(tmp_path_factory):
+    out = str(tmp_path_factory.mktemp("host") / "window_host.so")
+    subprocess.run(["g++", "-O2", "-shared", "-fPIC", "-std=c++17", "-w", "-D__HIP_PLATFORM_AMD__",
+                    "-I", os.path.join(ROCM, "include"), "-I", os.path.join(ROOT, "include"),
+                    "-I", os.path.join(ROOT, "paper_1910_11872_amd", "csrc"),
+                    os.path.join(HERE, "window_host.cpp"), "-o", out], check=True, timeout=300)
+    return ctypes.CDLL(out)
+
+
+def ptr(a):
+    return a.ctypes.data_as(ctypes.c_void_p)
+
+
+def f32(a):
+    return np.ascontiguousarray(a, np.float32)
+
+
+def wrap(a):
+    return (a + np.pi) % (2 * np.pi) - np.pi
+
+
+def unitary(L):
+    """Q: u1 = Q v."""
+    m, o = L // 2, L - L // 2
+    Q = np.zeros((L, L), complex)
+    for i in range(m):
+        Q[i, i] = Q[L - 1 - i, i] = 1 / np.sqrt(2)
+        Q[i, o + i], Q[L - 1 - i, o + i] = 1j / np.sqrt(2), -1j / np.sqrt(2)
+    if L & 1:
+        Q[m, m] = 1
+    return Q
+
+
+def real_form(S):
+    """Trace-normalised T of snapshots S (n, L, K), and the lag-1 sums."""
+    Q = unitary(S.shape[1])
+    R = S @ S.conj().transpose(0, 2, 1)
+    T = (Q.conj().T @ (R + R[:, ::-1, ::-1].conj()) @ Q).real
+    return T / np.trace(T, axis1=1, axis2=2)[:, None, None], (S[:, :-1].conj() * S[:, 1:]).sum((1, 2))
+
+
+def line_snapshots(rng, w, L, N, snr):
+    """Snapshots of noisy tones of N samples at frequencies w."""
+    n = len(w)
+    x = np.exp(1j * (w[:, None] * np.arange(N) + rng.uniform(0, 2 * np.pi, (n, 1))))
+    x = x + 10 ** (-snr / 20) / np.sqrt(2) * (rng.standard_normal((n, N)) + 1j * rng.standard_normal((n, N)))
+    return np.stack([x[:, i:i + N - L + 1] for i in range(L)], 1)
+
+
+def signal_vectors(rng, w, L, N, snr):
+    """FP32 signal vectors (real form) of noisy tones."""
+    T, _ = real_form(line_snapshots(rng, w, L, N, snr))
+    return f32(np.linalg.eigh(T)[1][:, :, -1])
+
+
+def root_omega(v, L):
+    """omega of each vector's pair nearest the circle, all roots in FP64."""
+    out = np.empty(len(v))
+    for t, u in enumerate(v.astype(float) @ unitary(L).T):
+        u = u / np.linalg.norm(u)
+        c = np.array([np.sum(u[:L - k] * u[k:].conj()) for k in range(L)])
+        z = np.roots(np.concatenate([-c[:0:-1].conj(), [L - c[0].real], -c[1:]])[::-1])
+        i = np.argmin(np.abs(np.abs(z) - 1))
+        d = np.abs(z - 1 / z[i].conj())
+        d[i] = np.inf
+        out[t] = np.angle(z[i] + z[np.argmin(d)])
+    return out
+
+
+@pytest.mark.parametrize("L,N,snr", [(2, 8, 14), (4, 16, 10), (6, 32, 8), (7, 24, 8), (8, 24, 8)])
+@pytest.mark.parametrize("lo,hi", [(0.0, 0.006), (0.006, 0.05)])
+def test_closed_form_near_pi(host, L, N, snr, lo, hi):
+    """Frequencies within lo .. hi of +-pi, the guess a few 1e-3 off the peak in directions that carry
+    the hardware's sine and cosine error.  Tolerance: atan2f and the correction (one unit each), their
+    sum and the wrap by 2 pi (half a unit each and 1.7e-7) at 2.4e-7 per unit: 9e-7."""
+    rng = np.random.default_rng(int(100 * L + 1000 * hi))
+    n = 1500
+    w = wrap(np.pi - rng.uniform(lo, hi, n) * rng.choice([-1, 1], n))
+    v = signal_vectors(rng, w, L, N, snr)
+    cw, sw = f32(np.cos(w) + rng.uniform(-5e-7, 5e-7, n)), f32(np.sin(w) + rng.uniform(-5e-7, 5e-7, n))
+    omega, ok = np.empty(n, np.float32), np.empty(n, np.uint8)
+    assert host.host_tone(L, ptr(v), ptr(cw), ptr(sw), n, ptr(omega), ptr(ok)) == 0
+    ok = ok.astype(bool)
+    assert ok.mean() > 0.9
+    d = np.abs(wrap(omega.astype(float) - root_omega(v, L)))[ok]
+    assert d.max() <= 9e-7, (d.max(), np.mean(d > 9e-7))
