@@ -20,7 +20,7 @@
  *   - signal/noise eigen-split with a one-dimensional signal subspace
  *     (Eq. 6-11): the top eigenvector of the real form of the covariance,
  *     by power iteration where an a-posteriori bound proves it within
- *     1e-5 rad, else by a tridiagonal solver (the power iteration starts
+ *     6e-6 rad, else by a tridiagonal solver (the power iteration starts
  *     at a line window's lag-1 phase, at a block window's summed lag-1
  *     phase, or at the surrogate's prediction);
  *   - root-MUSIC polynomial a(z)^H Un Un^H a(z) (Eq. 12) from the diagonal
@@ -253,7 +253,7 @@ bm_status bosmusic_get_stats(bosmusic_t h, bosmusic_stats* out, int32_t reset, v
  * one window in 32 of a line and its estimate w_hat serves those 32.  w_hat
  * seeds a power iteration on the window's FB-averaged covariance (in its
  * real form, paper Eq. 6-11) for the signal eigenvector u1, accepted once an
- * a-posteriori bound proves it within 1e-5 rad of the top eigenvector and
+ * a-posteriori bound proves it within 6e-6 rad of the top eigenvector and
  * the MUSIC null spectrum 1 - |u1^H a(w_hat)|^2 / L at the prediction is at
  * most tau.  Any other window takes the plain eigen-split.  From u1 on every
  * window follows the plain path (polynomial, Eq. 12-14; the proven pair or

@@ -160,11 +160,11 @@ __device__ __forceinline__ void block_omega(FS S, const RootTemplate& tmpl, bool
         return;
     }
     if constexpr (WHOLE) {
-        window_omega_Ts<L, JACOBI>(T, hc, hs, tmpl, full_roots, __builtin_nanf(""), omega, flag, ls);
+        window_omega_Ts<L, JACOBI>(T, hc, hs, kPowerTolBlock, tmpl, full_roots, __builtin_nanf(""), omega, flag, ls);
     } else {
         float v[L], nu, cw, sw;
         int steps = 0;
-        bool ok = power_top_eigvec<L>(T, hc, hs, kPowerMinSteps, kPowerMaxSteps, kPowerTol, v, steps, nu);
+        bool ok = power_top_eigvec<L>(T, hc, hs, kPowerMinSteps, kPowerMaxSteps, kPowerTolBlock, v, steps, nu);
         const unsigned left = ok ? kPendingRoot : kPendingEig;
         if (ok) {
             guess_direction<L>(v, cw, sw);
@@ -498,7 +498,7 @@ __global__ __launch_bounds__(kTileLanes) void block_rest_kernel(RmBatch B, int c
                 int steps = 0;
                 bool have = false;
                 if (!(flag[e] & kNoPower))
-                    have = power_top_eigvec<L>(T, hc, hs, kPowerMinSteps, kPowerMaxSteps, kPowerTol, v, steps, nu);
+                    have = power_top_eigvec<L>(T, hc, hs, kPowerMinSteps, kPowerMaxSteps, kPowerTolBlock, v, steps, nu);
                 if (have) {
                     ls.power += 1;
                     ls.eig_its += steps;

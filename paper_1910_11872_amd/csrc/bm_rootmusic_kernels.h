@@ -16,7 +16,7 @@
 //               signal subspace).  Power iteration on T, shifted by the
 //               mean of its other eigenvalues, from
 //               the steering vector of the window's lag-1 phase, kept when
-//               an a-posteriori bound proves it within 1e-5 rad of the top
+//               an a-posteriori bound proves it within 6e-6 rad of the top
 //               eigenvector (2-3 steps at 10 dB).  Otherwise: Householder
 //               reduction to tridiagonal form, Newton's
 //               method from above on the characteristic polynomial

@@ -16,7 +16,7 @@
 //   4. lag sums, covariance and the real symmetric T = Q^H R_fb Q as in the
 //      plain kernel; the top eigenvector by power iteration from the steering
 //      vector of omega_hat, accepted once an a-posteriori bound proves it
-//      within 1e-5 of the eigenvector and the MUSIC null spectrum at
+//      within 6e-6 rad of the eigenvector and the MUSIC null spectrum at
 //      omega_hat is below tau; otherwise the plain eigen-split (Householder,
 //      Newton, inverse iteration);
 //   5. the plain path's root pair (closed form, certified, or from all roots)

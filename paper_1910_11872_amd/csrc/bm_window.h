@@ -1393,13 +1393,17 @@ __device__ __forceinline__ void T_from_snapshots(int K, F snap, Sym<L>& T, float
 // as much and l2 is their spread.  The eigenvectors and the residual are T's
 // own, and everything above holds with rho, l2 and tr T^2 of the shifted
 // matrix, for any mu (the gap is compared with the unshifted rho).  The FP32
-// rounding of tr T^2 - rho^2 is added to it.  Numpy trials: steps of a wave's
-// slowest lane 3.7 -> 3.2 at 10 dB (L = 6, 8; N = 32), 5.2 -> 4.6 at 7 dB (L =
-// 8, N = 24), 7.1 -> 5.8 at 6 dB (L = 4, N = 16, where the windows that give up
-// fall from 2.7% to 0.4%), true angles of the accepted vectors 2.1e-6 -> 1.3e-6
-// rms; measured, 16 frames of 4096 x 4096 (L = 8) 21.75 -> 21.50 ms, the uneven
-// batch (5-20 dB) 6.96 -> 6.70, 20 frames with 11 x 11 blocks 4.75 -> 4.63.
-// T's diagonal is shifted in place, and shifted back when no step is accepted.
+// rounding of tr T^2 - rho^2 is added to it.  A tighter l2 also accepts a vector
+// a step earlier, so the angle to prove is 6e-6 for line windows and 4e-6 for
+// block windows where the plain iteration had 1e-5 (kPowerTol, kPowerTolBlock):
+// with 1e-5 the accepted vectors were up to 7 times further off than the plain
+// iteration's (17 x 17 blocks at 9 dB; 1.4 times, L = 8, N = 48 at 8 dB).  rms
+// angle against the plain iteration's at worst, this code on the host, L = 3-17,
+// N from L to 64, 5-20 dB: lines 1.02 at 7e-6, 0.92 at 6e-6; blocks 1.5 at 5e-6,
+// 0.7 at 4e-6.  Steps of a wave's slowest lane, means over 5-16 dB: L = 8 lines
+// 3.62 plain, 3.32 at 6e-6; over 8-20 dB: 15 x 15 blocks 2.41 and 2.39 at 4e-6.
+// T's diagonal is shifted in place, and shifted back (to within a rounding of
+// its largest entries, 6e-8) when no step is accepted.
 constexpr float kPowerRound = 4e-7f;   // FP32 rounding of tr T^2 - rho^2, both at most 1
 template <int L>
 __device__ __forceinline__ bool power_top_eigvec(Sym<L>& T, float hc, float hs, int min_steps, int max_steps,
@@ -1436,9 +1440,9 @@ __device__ __forceinline__ bool power_top_eigvec(Sym<L>& T, float hc, float hs, 
     for (int i = 0; i < L; ++i) T.a[i][i] -= mu;
 #pragma unroll
     for (int i = 0; i < L; ++i) v[i] = v0[i];
-    // Unnormalised steps: the trace is 1, so the shifted lambda_1 stays above
-    // 1/L^2 and max_steps steps shrink the iterate by at most L^-(2 max_steps),
-    // inside FP32's range.
+    // Unnormalised steps.  The shifted lambda_1 is smallest for T = I / L, 1 / (L (1 + sqrt L)), so
+    // the top component keeps inside FP32's range over max_steps steps; an iterate that shrinks
+    // to nothing because it has none fails the test of ivv and goes to the other solver.
     bool ok = false;
     for (int it = 0; it < max_steps; ++it) {
         ++steps;
@@ -1537,10 +1541,12 @@ __device__ __forceinline__ void lag1_half_angle(const Cov<L>& R, float& hc, floa
 }
 
 // Power iteration of the windows: a start at the lag-1 direction, the
-// first test after two steps, at most eight, and a proven angle below 1e-5.
+// first test after two steps, at most eight, and a proven angle below kPowerTol
+// (line windows) or kPowerTolBlock (the reasons: power_top_eigvec).
 constexpr int kPowerMinSteps = 2;
 constexpr int kPowerMaxSteps = 8;
-constexpr float kPowerTol = 1e-5f;
+constexpr float kPowerTol = 6e-6f;
+constexpr float kPowerTolBlock = 4e-6f;
 
 // The signal eigenvector of T by the tridiagonal solver (Jacobi with
 // JACOBI); false, with BM_FLAG_DEGENERATE, when the subspace is not determined.
@@ -1556,11 +1562,11 @@ __device__ __forceinline__ bool signal_eigvec_T(Sym<L>& T, float (&v)[L], unsign
 
 // The window from its trace-normalised T and a start e^{j w/2} = (hc, hs) at
 // the window's lag-1 phase: the signal eigenvector first by power iteration
-// (power_top_eigvec: accepted only with a proven angle below 1e-5 rad and a
+// (power_top_eigvec: accepted only with an angle proven below `tol` and a
 // proven gap), else by the tridiagonal solver (Jacobi alone with JACOBI);
 // then the polynomial, the root pair and omega.
 template <int L, bool JACOBI>
-__device__ __forceinline__ void window_omega_Ts(Sym<L>& T, float hc, float hs, const RootTemplate& tmpl,
+__device__ __forceinline__ void window_omega_Ts(Sym<L>& T, float hc, float hs, float tol, const RootTemplate& tmpl,
                                                 bool full_roots, float wprev, float& omega, unsigned& flag,
                                                 LaneStats& ls) {
     ls.counted += 1;
@@ -1570,7 +1576,7 @@ __device__ __forceinline__ void window_omega_Ts(Sym<L>& T, float hc, float hs, c
     if (!JACOBI) {
         float nu;
         int steps = 0;
-        have = power_top_eigvec<L>(T, hc, hs, kPowerMinSteps, kPowerMaxSteps, kPowerTol, v, steps, nu);
+        have = power_top_eigvec<L>(T, hc, hs, kPowerMinSteps, kPowerMaxSteps, tol, v, steps, nu);
         if (have) {
             ls.power += 1;
             ls.eig_its += steps;
@@ -1591,7 +1597,7 @@ __device__ __forceinline__ void window_omega(const Cov<L>& R, const RootTemplate
         flag |= BM_FLAG_UNDEFINED;
         return;
     }
-    window_omega_Ts<L, JACOBI>(T, hc, hs, tmpl, full_roots, wprev, omega, flag, ls);
+    window_omega_Ts<L, JACOBI>(T, hc, hs, kPowerTol, tmpl, full_roots, wprev, omega, flag, ls);
 }
 
 // The rest of the window from the top eigenvector v of T (unit, real form of

@@ -98,3 +98,59 @@ def test_closed_form_near_pi(host, L, N, snr, lo, hi):
     assert ok.mean() > 0.9
     d = np.abs(wrap(omega.astype(float) - root_omega(v, L)))[ok]
     assert d.max() <= 9e-7, (d.max(), np.mean(d > 9e-7))
+
+
+def plain_power(T, c1, tol=1e-5):
+    """The power iteration on T itself (no shift), FP64, from the lag-1 direction: each window's vector
+    of the first step (from the second on, of eight) whose angle the residual bound proves below tol."""
+    n, L = T.shape[:2]
+    s = np.arange(L) - (L - 1) / 2
+    a = np.exp(1j * np.angle(c1)[:, None] * s) / np.sqrt(L)
+    v = (a @ unitary(L).conj()).real
+    t2 = (T ** 2).sum((1, 2))
+    done, out = np.zeros(n, bool), np.full((n, L), np.nan)
+    for it in range(8):
+        y = np.einsum("nij,nj->ni", T, v)
+        rho = np.einsum("ni,ni->n", v, y)
+        r = np.linalg.norm(y - rho[:, None] * v, axis=1)
+        l2 = np.sqrt(np.maximum(t2 - rho ** 2, 0))
+        sb = r / np.maximum(rho - l2, 1e-30)
+        ok = ~done & (rho > l2) & (sb <= 0.5) & (l2 / rho * sb * np.sqrt(4 / 3) <= tol) & (it >= 1)
+        v = y / np.linalg.norm(y, axis=1)[:, None]
+        out[ok] = v[ok]
+        done |= ok
+    return out, done
+
+
+def angles(v, top):
+    s = np.sign(np.einsum("ni,ni->n", v, top))
+    return np.linalg.norm(v - top * s[:, None], axis=1)
+
+
+@pytest.mark.parametrize("L,N,snr", [(4, 32, 8), (6, 32, 8), (8, 48, 8), (6, 6, 11), (8, 8, 11), (9, 9, 10), (11, 11, 10),
+                                     (13, 13, 10), (15, 15, 9), (17, 17, 9), (11, 11, 16)])
+def test_shifted_power_iteration_is_as_accurate_as_the_plain_one(host, L, N, snr):
+    """The shift tightens the bound as well as the convergence: the vectors it accepts are no further
+    from the top eigenvector than those of the plain iteration accepted at 1e-5 (or within what FP32
+    leaves of any vector, 1.5e-7).  N = L: block windows."""
+    rng = np.random.default_rng(17 * L + N)
+    n = 3000
+    w = rng.uniform(0.3, 1.6, n)
+    if N > L:
+        S = line_snapshots(rng, w, L, N, snr)
+    else:
+        y, x = np.mgrid[:L, :L]
+        S = np.exp(1j * (rng.uniform(0.02, 0.3, (n, 1, 1)) * y + w[:, None, None] * x))
+        S = S + 10 ** (-snr / 20) / np.sqrt(2) * (rng.standard_normal(S.shape) + 1j * rng.standard_normal(S.shape))
+        S = S.transpose(0, 2, 1)
+    T, c1 = real_form(S)
+    T = f32(T)
+    top = np.linalg.eigh(T.astype(float))[1][:, :, -1]
+    v, steps, ok = np.empty((n, L), np.float32), np.empty(n, np.int32), np.empty(n, np.uint8)
+    cr, ci = f32(c1.real), f32(c1.imag)
+    assert host.host_power(L, ptr(T), ptr(cr), ptr(ci), n, int(N == L), ptr(v), ptr(steps), ptr(ok)) == 0
+    ok = ok.astype(bool)
+    ref, done = plain_power(T.astype(float), c1)
+    assert ok.mean() >= done.mean() - 0.01
+    rms = np.sqrt(np.mean(angles(v, top)[ok] ** 2))
+    assert rms <= max(np.sqrt(np.mean(angles(ref, top)[done] ** 2)), 1.5e-7), (rms, steps[ok].mean())

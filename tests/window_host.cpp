@@ -54,9 +54,9 @@ void window(const float* v, const float* wprev, int n, float* omega, int* steps)
 }
 
 // power_top_eigvec of n trace-normalised matrices T (L x L each) as the windows call it,
-// from the lag-1 sums (c1r, c1i).
+// from the lag-1 sums (c1r, c1i); block: as block windows do.
 template <int L>
-void power(const float* T, const float* c1r, const float* c1i, int n, float* v, int* steps, uint8_t* ok) {
+void power(const float* T, const float* c1r, const float* c1i, int n, int block, float* v, int* steps, uint8_t* ok) {
     for (int q = 0; q < n; ++q) {
         Sym<L> t;
         for (int i = 0; i < L; ++i)
@@ -64,7 +64,8 @@ void power(const float* T, const float* c1r, const float* c1i, int n, float* v, 
         float a[L], nu, hc, hs;
         int s = 0;
         half_angle_of(c1r[q], c1i[q], hc, hs);
-        ok[q] = power_top_eigvec<L>(t, hc, hs, kPowerMinSteps, kPowerMaxSteps, kPowerTol, a, s, nu);
+        ok[q] = power_top_eigvec<L>(t, hc, hs, kPowerMinSteps, kPowerMaxSteps, block ? kPowerTolBlock : kPowerTol, a,
+                                    s, nu);
         steps[q] = s;
         std::memcpy(v + (int64_t)q * L, a, sizeof a);
     }
@@ -98,8 +99,9 @@ int host_tone(int L, const float* v, const float* cw, const float* sw, int n, fl
 #define ARGS (v, wprev, n, omega, steps)
 int host_window(int L, const float* v, const float* wprev, int n, float* omega, int* steps) { BY_SIZE(window) }
 #undef ARGS
-#define ARGS (T, c1r, c1i, n, v, steps, ok)
-int host_power(int L, const float* T, const float* c1r, const float* c1i, int n, float* v, int* steps, uint8_t* ok) {
+#define ARGS (T, c1r, c1i, n, block, v, steps, ok)
+int host_power(int L, const float* T, const float* c1r, const float* c1i, int n, int block, float* v, int* steps,
+               uint8_t* ok) {
     BY_SIZE(power)
 }
 #undef ARGS
