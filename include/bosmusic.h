@@ -148,10 +148,10 @@ typedef struct {
     /* Temporal warm start (optional; line windows; ignored by BM_SURROGATE): the omega maps of
      * the previous frame of a time-lapsed series, the same size, row stride =
      * width (the paper's premise that the phase changes little between
-     * successive frames, Sec. 1 and 4).  Where the previous frequency at the
-     * pixel is finite, the search for the window's signal root
-     * starts in its direction instead of the window's own lag-1 direction.
-     * The pair, hence omega, is the same either way (up to
+     * successive frames, Sec. 1 and 4).  A window that the closed form does not
+     * serve starts the search for its signal root in the direction of the
+     * previous frequency at the pixel, where that is finite, instead of its own
+     * lag-1 direction.  The pair, hence omega, is the same either way (up to
      * rounding); only the steps to it change.  NULL: no warm start. */
     const float* prev_omega_x;
     const float* prev_omega_y;

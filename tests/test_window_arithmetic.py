@@ -154,3 +154,23 @@ def test_shifted_power_iteration_is_as_accurate_as_the_plain_one(host, L, N, snr
     assert ok.mean() >= done.mean() - 0.01
     rms = np.sqrt(np.mean(angles(v, top)[ok] ** 2))
     assert rms <= max(np.sqrt(np.mean(angles(ref, top)[done] ** 2)), 1.5e-7), (rms, steps[ok].mean())
+
+
+@pytest.mark.parametrize("L,N,snr", [(4, 16, 10), (6, 32, 8), (7, 15, 12), (8, 24, 8)])
+@pytest.mark.parametrize("shift", [0.0, 0.1, -2.0])
+def test_warm_start_keeps_the_closed_form(host, L, N, snr, shift):
+    """A window that the closed form serves takes it whatever the previous frame's frequency was: the
+    same omega in the same one step each as without a warm start."""
+    rng = np.random.default_rng(L * N)
+    n = 2000
+    w = rng.uniform(0.3, 1.6, n)
+    v = signal_vectors(rng, w, L, N, snr)
+    out = []
+    for prev in (np.full(n, np.nan), w + shift):
+        prev, omega, steps = f32(prev), np.empty(n, np.float32), np.empty((n, 2), np.int32)
+        assert host.host_window(L, ptr(v), ptr(prev), n, ptr(omega), ptr(steps)) == 0
+        out.append((omega, steps))
+    closed = (out[0][1] == 1).all(1)
+    assert closed.mean() > 0.99
+    assert np.array_equal(out[0][1][closed], out[1][1][closed])
+    assert np.array_equal(out[0][0][closed], out[1][0][closed])
