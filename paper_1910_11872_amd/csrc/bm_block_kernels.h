@@ -184,36 +184,54 @@ __device__ __forceinline__ void block_omega(FS S, const RootTemplate& tmpl, bool
 }
 
 // Rows i0 .. i1-1 of the block phase's sum; `at(i, j)` returns G[i][j] of the
-// window.  The hardware sine and cosine: arguments stay within |w| (L/2) <=
-// 8.5 pi, where their error (~1e-6) is far below the phase tolerance, and the
-// library's large-argument reduction would hold registers the whole kernel
-// pays for.
-template <int L, typename FG>
-__device__ __forceinline__ float2 block_phase_rows(FG at, float wx, float wy, int i0, int i1) {
-    constexpr int h = L / 2;
+// window, (exr, exi)[j] = e^{-j wx (j-h)}.  The hardware sine and cosine: arguments
+// stay within |w| (L/2) <= 8.5 pi, where their error (~1e-6) is far below the phase
+// tolerance, and the library's large-argument reduction would hold registers the
+// whole kernel pays for.  The rows are not unrolled (one 1850 x 700 frame, 15 x 15:
+// 295 us, 299 unrolled).
+template <int L>
+struct PhaseRow {
     float exr[L], exi[L];
-#pragma unroll
-    for (int j = 0; j < L; ++j) {
-        float sn, cs;
-        __sincosf(wx * (float)(j - h), &sn, &cs);
-        exr[j] = cs;
-        exi[j] = -sn;
-    }
-    float ar = 0.f, ai = 0.f;
-    for (int i = i0; i < i1; ++i) {
-        float rr = 0.f, ri = 0.f;     // sum_j G[i][j] e^{-j wx (j-h)}
+    __device__ __forceinline__ explicit PhaseRow(float wx) {
 #pragma unroll
         for (int j = 0; j < L; ++j) {
-            const float2 v = at(i, j);
-            rr = fmaf(v.x, exr[j], fmaf(-v.y, exi[j], rr));
-            ri = fmaf(v.x, exi[j], fmaf(v.y, exr[j], ri));
+            float sn, cs;
+            __sincosf(wx * (float)(j - L / 2), &sn, &cs);
+            exr[j] = cs;
+            exi[j] = -sn;
         }
-        float sn, cs;
-        __sincosf(wy * (float)(i - h), &sn, &cs);   // times e^{-j wy (i-h)}
-        ar = fmaf(rr, cs, fmaf(ri, sn, ar));
-        ai = fmaf(ri, cs, fmaf(-rr, sn, ai));
     }
-    return make_float2(ar, ai);
+    template <typename FG>
+    __device__ __forceinline__ float2 sum(FG at, float wy, int i0, int i1) const {
+        float ar = 0.f, ai = 0.f;
+#pragma unroll 1
+        for (int i = i0; i < i1; ++i) {
+            float rr = 0.f, ri = 0.f;     // sum_j G[i][j] e^{-j wx (j-h)}
+#pragma unroll
+            for (int j = 0; j < L; ++j) {
+                const float2 v = at(i, j);
+                rr = fmaf(v.x, exr[j], fmaf(-v.y, exi[j], rr));
+                ri = fmaf(v.x, exi[j], fmaf(v.y, exr[j], ri));
+            }
+            float sn, cs;
+            __sincosf(wy * (float)(i - L / 2), &sn, &cs);   // times e^{-j wy (i-h)}
+            ar = fmaf(rr, cs, fmaf(ri, sn, ar));
+            ai = fmaf(ri, cs, fmaf(-rr, sn, ai));
+        }
+        return make_float2(ar, ai);
+    }
+};
+
+// The block phase from the sums of the rows below L/2 and of the others: two lane
+// groups may take one each, and the order is the same where one lane takes both,
+// so a frame's phase does not depend on the batch that it shares a launch with.
+__device__ __forceinline__ float phase_of(float2 low, float2 high) { return atan2f(low.y + high.y, low.x + high.x); }
+
+template <int L, typename FG>
+__device__ __forceinline__ float block_phase(FG at, float wx, float wy) {
+    const PhaseRow<L> e(wx);
+    const float2 low = e.sum(at, wy, 0, L / 2);
+    return phase_of(low, e.sum(at, wy, L / 2, L));
 }
 
 // Waves per SIMD asked of the compiler: what the LDS of the blocks lets be
@@ -322,16 +340,13 @@ void block_tile_kernel(RmBatch B) {
             const bool ok = J.phase && finitef(wx) && finitef(wy);
             if (ok) {
                 const float2* s = sg + ty * BT::GP + tx;
-                sum = block_phase_rows<L>([&](int r, int c) { return s[r * BT::GP + c]; }, wx, wy, half ? L / 2 : 0,
+                sum = PhaseRow<L>(wx).sum([&](int r, int c) { return s[r * BT::GP + c]; }, wy, half ? L / 2 : 0,
                                           half ? L : L / 2);
             }
             if (half == 1) xp[t] = sum;
             __syncthreads();
             if (half == 0 && inside) {
-                if (J.phase) {
-                    const float2 q = xp[t];
-                    J.phase[o] = ok ? atan2f(sum.y + q.y, sum.x + q.x) : __builtin_nanf("");
-                }
+                if (J.phase) J.phase[o] = ok ? phase_of(sum, xp[t]) : __builtin_nanf("");
                 if (J.flags) J.flags[fo] = (uint8_t)((dx ? f2[0] : 0u) | ((dy ? xf[t] : 0u) << 4));
             }
         }
@@ -354,9 +369,7 @@ void block_tile_kernel(RmBatch B) {
                 float ph = __builtin_nanf("");
                 if (finitef(w2[0]) && finitef(w2[1])) {
                     const float2* s = sg + ty * BT::GP + tx;
-                    const float2 q =
-                        block_phase_rows<L>([&](int r, int c) { return s[r * BT::GP + c]; }, w2[0], w2[1], 0, L);
-                    ph = atan2f(q.y, q.x);
+                    ph = block_phase<L>([&](int r, int c) { return s[r * BT::GP + c]; }, w2[0], w2[1]);
                 }
                 J.phase[o] = ph;
             }
@@ -530,8 +543,7 @@ __global__ __launch_bounds__(kTileLanes) void block_rest_kernel(RmBatch B, int c
                 if (finitef(wx) && finitef(wy)) {
                     const float2* g = J.gamma + (int64_t)(line - h) * J.gamma_ls + (p - h);
                     const int64_t gl = J.gamma_ls;
-                    const float2 q = block_phase_rows<L>([&](int r, int c) { return g[r * gl + c]; }, wx, wy, 0, L);
-                    ph = atan2f(q.y, q.x);
+                    ph = block_phase<L>([&](int r, int c) { return g[r * gl + c]; }, wx, wy);
                 }
                 J.phase[o] = ph;
             }
