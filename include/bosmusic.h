@@ -203,13 +203,15 @@ bm_status bosmusic_destroy(bosmusic_t h);
  * launch, one batched analytic-signal launch and one root-MUSIC launch per
  * distinct L (with BM_OPT_GRAPH: one replay of a cached hipGraph holding them,
  * the per-L launches on forked streams).  Without BM_OPT_GRAPH and
- * BM_OPT_TIMING, a group of two or more frames runs as two halves on
- * `stream` and a second stream of the handle: the second half's transpose
- * and analytic launches run beside the first half's root-MUSIC launch, its
- * root-MUSIC launch after the first half's; `stream` waits for the second
- * stream before the call returns, so every output is ordered on `stream`
- * as if the work had been enqueued there alone.  (Not when the second half
- * has a real line longer than 2048 samples whose length is not a power of
+ * BM_OPT_TIMING, a group of two or more frames whose line windows cover 64
+ * million pixel directions or more runs as two halves on `stream` and a second
+ * stream of the handle: the second half's transpose and analytic launches run
+ * beside the first half's root-MUSIC launch, its root-MUSIC launch after the
+ * first half's; `stream` waits for the second stream before the call returns,
+ * so every output is ordered on `stream` as if the work had been enqueued there
+ * alone, and the results do not depend on the split.  (Not when the second half
+ * has a real line whose transform is longer than 2048 samples -- the line's
+ * length, twice that where it has a prime factor above 13 -- and not a power of
  * two: the analytic step's 1024-thread blocks for it cannot run beside a
  * root-MUSIC launch, so the group runs in `stream` alone.)  The job tables of a group are
  * uploaded from pinned host memory on `stream`; the call may wait for the

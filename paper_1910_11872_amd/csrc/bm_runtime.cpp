@@ -426,16 +426,18 @@ bm_status validate_frame(bosmusic_s* h, const bosmusic_frame& f, int idx) {
     return BM_OK;
 }
 
-// Pixels times directions of a group from which its two halves run on two
-// streams.  The split hides the second half's transposes and analytic step
-// behind the first half's root-MUSIC launch, and costs a second set of
-// launches, four events and the drained chip at the end of each half's launch.
-// One launch against two halves: 2 x 256^2 34 against 93 us, 2 x 1024^2 140
-// against 180, 20 x 1024^2 with 11 x 11 blocks 1.65 against 1.80 ms, 32 x
-// 1024^2 1.78 against 1.85; 12 x 2048^2 (L = 4) 2.05 against 1.97, 100 x
-// 1024^2 5.67 against 5.50, 16 x 4096^2 16.90 against 16.79.  Line windows
-// break even at about 80 M, block windows at 130 M.
-constexpr int64_t kSplitWork = 96000000;
+// Pixels times directions of a group's line windows from which its two halves run
+// on two streams.  The split hides the second half's transposes and analytic step
+// behind the first half's root-MUSIC launch, and costs a second set of launches,
+// four events and the drained chip at the end of each half's launch.  One launch
+// against two halves, line windows: 2 x 256^2 34 against 93 us, 16 x 1024^2 (L = 3)
+// 628 against 637, 24 x 1024^2 936 against 931, 36 x 1024^2 1442 against 1386, 70 x
+// 1024^2 (L = 6) 4.06 against 3.93 ms, 12 x 2048^2 (L = 4) 2.07 against 1.97; even
+// between 42 and 63 M (the surrogate and 1850 x 700 frames 1.01 at 63 M, 0.98 at 100).
+// Block windows have no transposes and one analytic step for both directions: halves
+// gain nothing (0.99 to 1.01 from 40 to 200 frames of 1024^2, L = 4 to 17; 40 frames
+// with 15 x 15 blocks 7.87 against 8.10 ms), so they do not count.
+constexpr int64_t kSplitWork = 64000000;
 
 size_t frame_ws_bytes(const bosmusic_frame& f) {
     const size_t px = (size_t)f.width * (size_t)f.height;
@@ -1506,8 +1508,9 @@ bm_status bosmusic_demodulate(bosmusic_t h, const bosmusic_frame* frames, int32_
         for (auto& g : groups) {
             int64_t work = 0;
             for (int i = g.first; i < g.second; ++i)
-                work += (int64_t)frames[i].width * frames[i].height *
-                        (((frames[i].dirs & BM_DIR_X) != 0) + ((frames[i].dirs & BM_DIR_Y) != 0));
+                if (!(frames[i].dirs & BM_BLOCK))
+                    work += (int64_t)frames[i].width * frames[i].height *
+                            (((frames[i].dirs & BM_DIR_X) != 0) + ((frames[i].dirs & BM_DIR_Y) != 0));
             if (g.second - g.first >= 2 && work >= kSplitWork && !(h->options & BM_OPT_TIMING)) {
                 // two halves pipelined on two streams (results do not depend on the split);
                 // with BM_OPT_TIMING each root-MUSIC launch runs alone, timed by its events
