@@ -41,10 +41,9 @@ namespace {
 
 constexpr int kTile = kBlockTile;                       // pixels per side of a tile
 constexpr int kTileLanes = kTile * kTile;
-// NaN payloads of a window left to block_rest_kernel: the power iteration was
-// not proven (the other eigen solvers remain), or the window is not one tone.
-constexpr unsigned kPendingEig = 0x7FC0B10Cu, kPendingRoot = 0x7FC0B10Du;
-__device__ __forceinline__ bool pending(float w) { return (__float_as_uint(w) | 1u) == kPendingRoot; }
+// NaN payload of a window left to block_rest_kernel.
+constexpr unsigned kPending = 0x7FC0B10Cu;
+__device__ __forceinline__ bool pending(float w) { return __float_as_uint(w) == kPending; }
 
 template <int L>
 struct BlockTile {
@@ -164,11 +163,10 @@ __device__ __forceinline__ void block_omega(FS S, const RootTemplate& tmpl, bool
     } else {
         float v[L], nu, cw, sw;
         int steps = 0;
-        bool ok = power_top_eigvec<L>(T, hc, hs, kPowerMinSteps, kPowerMaxSteps, kPowerTolBlock, v, steps, nu);
-        const unsigned left = ok ? kPendingRoot : kPendingEig;
+        bool ok = power_top_eigvec<L>(T, hc, hs, kPowerMinSteps, power_max_steps_big(L), kPowerTolBlock, v, steps, nu);
         if (ok) {
             guess_direction<L>(v, cw, sw);
-            ok = tone_omega<L>(v, cw, sw, omega);
+            ok = tone_omega<L, true>(v, cw, sw, omega);
         }
         if (ok) {
             ls.counted += 1;
@@ -178,7 +176,7 @@ __device__ __forceinline__ void block_omega(FS S, const RootTemplate& tmpl, bool
             ls.pair_its += 1;
             ls.accepted += 1;
         } else {
-            omega = __uint_as_float(left);
+            omega = __uint_as_float(kPending);
         }
     }
 }
@@ -201,15 +199,27 @@ struct PhaseRow {
             exi[j] = -sn;
         }
     }
-    template <typename FG>
+    // AHEAD: the next row's loads in flight meanwhile (samples in device memory).
+    template <bool AHEAD, typename FG>
     __device__ __forceinline__ float2 sum(FG at, float wy, int i0, int i1) const {
         float ar = 0.f, ai = 0.f;
+        float2 next[L];
+        auto fetch = [&](int i) {
+#pragma unroll
+            for (int j = 0; j < L; ++j) next[j] = at(i, j);
+        };
+        if (AHEAD) fetch(i0);
 #pragma unroll 1
         for (int i = i0; i < i1; ++i) {
             float rr = 0.f, ri = 0.f;     // sum_j G[i][j] e^{-j wx (j-h)}
+            float2 row[L];
+            if (!AHEAD) fetch(i);
+#pragma unroll
+            for (int j = 0; j < L; ++j) row[j] = next[j];
+            if (AHEAD && i + 1 < i1) fetch(i + 1);
 #pragma unroll
             for (int j = 0; j < L; ++j) {
-                const float2 v = at(i, j);
+                const float2 v = row[j];
                 rr = fmaf(v.x, exr[j], fmaf(-v.y, exi[j], rr));
                 ri = fmaf(v.x, exi[j], fmaf(v.y, exr[j], ri));
             }
@@ -227,11 +237,11 @@ struct PhaseRow {
 // so a frame's phase does not depend on the batch that it shares a launch with.
 __device__ __forceinline__ float phase_of(float2 low, float2 high) { return atan2f(low.y + high.y, low.x + high.x); }
 
-template <int L, typename FG>
+template <int L, bool AHEAD, typename FG>
 __device__ __forceinline__ float block_phase(FG at, float wx, float wy) {
     const PhaseRow<L> e(wx);
-    const float2 low = e.sum(at, wy, 0, L / 2);
-    return phase_of(low, e.sum(at, wy, L / 2, L));
+    const float2 low = e.template sum<AHEAD>(at, wy, 0, L / 2);
+    return phase_of(low, e.template sum<AHEAD>(at, wy, L / 2, L));
 }
 
 // Waves per SIMD asked of the compiler: what the LDS of the blocks lets be
@@ -340,8 +350,8 @@ void block_tile_kernel(RmBatch B) {
             const bool ok = J.phase && finitef(wx) && finitef(wy);
             if (ok) {
                 const float2* s = sg + ty * BT::GP + tx;
-                sum = PhaseRow<L>(wx).sum([&](int r, int c) { return s[r * BT::GP + c]; }, wy, half ? L / 2 : 0,
-                                          half ? L : L / 2);
+                sum = PhaseRow<L>(wx).template sum<false>([&](int r, int c) { return s[r * BT::GP + c]; }, wy,
+                                                         half ? L / 2 : 0, half ? L : L / 2);
             }
             if (half == 1) xp[t] = sum;
             __syncthreads();
@@ -369,7 +379,7 @@ void block_tile_kernel(RmBatch B) {
                 float ph = __builtin_nanf("");
                 if (finitef(w2[0]) && finitef(w2[1])) {
                     const float2* s = sg + ty * BT::GP + tx;
-                    ph = block_phase<L>([&](int r, int c) { return s[r * BT::GP + c]; }, w2[0], w2[1]);
+                    ph = block_phase<L, false>([&](int r, int c) { return s[r * BT::GP + c]; }, w2[0], w2[1]);
                 }
                 J.phase[o] = ph;
             }
@@ -402,7 +412,7 @@ void block_tile_kernel(RmBatch B) {
 constexpr int kRestTiles = 16;
 constexpr int kRestScan = 4;           // marked tiles whose maps are read together
 constexpr int kRestChunk = 4;          // neighbouring tiles of a block's chunk
-constexpr unsigned kListed = 0x80u, kNoPower = 0x40u;
+constexpr unsigned kListed = 0x80u;
 
 template <int L, bool STATS>
 __global__ __launch_bounds__(kTileLanes) void block_rest_kernel(RmBatch B, int chunk) {
@@ -476,8 +486,7 @@ __global__ __launch_bounds__(kTileLanes) void block_rest_kernel(RmBatch B, int c
                     } else if (!pending(w2[u][dir])) {
                         continue;
                     }
-                    const bool tried = !B.full_roots && __float_as_uint(w2[u][dir]) == kPendingEig;
-                    flag[e] = (unsigned char)(kListed | (tried ? kNoPower : 0u));
+                    flag[e] = (unsigned char)kListed;
                     list[atomicAdd(&count, 1)] = (unsigned short)e;
                 }
                 if (B.full_roots && !valid) {
@@ -507,11 +516,12 @@ __global__ __launch_bounds__(kTileLanes) void block_rest_kernel(RmBatch B, int c
                 fl |= BM_FLAG_UNDEFINED;
             } else {
                 ls.counted += 1;
+                // what the tile kernel leaves was not proven there or took many steps: the
+                // tridiagonal solver at once (with every root wanted nothing was tried yet)
                 float v[L], nu;
                 int steps = 0;
-                bool have = false;
-                if (!(flag[e] & kNoPower))
-                    have = power_top_eigvec<L>(T, hc, hs, kPowerMinSteps, kPowerMaxSteps, kPowerTolBlock, v, steps, nu);
+                const bool have = B.full_roots && power_top_eigvec<L>(T, hc, hs, kPowerMinSteps, kPowerMaxSteps,
+                                                                      kPowerTolBlock, v, steps, nu);
                 if (have) {
                     ls.power += 1;
                     ls.eig_its += steps;
@@ -543,7 +553,7 @@ __global__ __launch_bounds__(kTileLanes) void block_rest_kernel(RmBatch B, int c
                 if (finitef(wx) && finitef(wy)) {
                     const float2* g = J.gamma + (int64_t)(line - h) * J.gamma_ls + (p - h);
                     const int64_t gl = J.gamma_ls;
-                    ph = block_phase<L>([&](int r, int c) { return g[r * gl + c]; }, wx, wy);
+                    ph = block_phase<L, true>([&](int r, int c) { return g[r * gl + c]; }, wx, wy);
                 }
                 J.phase[o] = ph;
             }

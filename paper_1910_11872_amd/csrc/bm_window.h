@@ -949,14 +949,25 @@ __device__ __forceinline__ void guess_direction(const float (&v)[L], float& cw, 
 // rounding of |v| makes of a double root there: the same formula gives the
 // mean angle of the two.  False (nothing written) when the window is not within
 // tone_s2 of a tone, the step to the peak is not small, the peak is not
-// reached to 3e-4 rad (beyond it the terms left out count), or k^2 T > 0.2
+// within 3e-4 rad of the root (beyond it the terms left out count), or k^2 T > 0.2
 // (beyond the series, and well inside the annulus).
 // Bound by VALU issue, so what counts is instructions: 40 in FP64 and about
 // 140 in FP32 at L = 8, against about 110 and 310 for the start, the FP32 and
 // FP64 Newton steps and their evaluations of P and P'.  Measured: 16 frames of
 // 4096 x 4096 (L = 8, N = 32) 21.50 -> 17.89 ms, the uneven batch 6.70 -> 4.71,
 // one 256 x 256 frame (L = 4) 37.4 -> 22.7 us.
-template <int L>
+//
+// The root lies xx from the peak where the spectrum is lopsided, by up to 1e-3
+// rad for windows over which the frequency bends (the diffusion front of a frame
+// of few lines).  AGAIN: beyond 3e-4 rad the moments are formed once more at w + a
+// + xx, where what remains of xx is far below that; otherwise such a window is
+// refused too.  Where a refused window waits for another kernel (blocks above 8 x
+// 8) the second expansion is worth far more than it costs: 20 frames of 1024 x
+// 1024 with 11 x 11 blocks 1.69 -> 1.58 ms, one 1850 x 700 frame with 15 x 15 295 ->
+// 253 us, one of 200 x 64 at 16 dB 80 -> 69; where the lane itself goes on with
+// Newton's method its loop costs the others 0.5 to 1.5% (100 of 1024 x 1024, L = 6
+// lines, 5.50 -> 5.58 ms; 16 of 4096 x 4096 17.76 -> 18.0).
+template <int L, bool AGAIN = false>
 __device__ __forceinline__ bool tone_omega(const float (&v)[L], float cw, float sw, float& omega) {
     constexpr int m = L / 2;
     constexpr int o = L - m;
@@ -1003,51 +1014,59 @@ __device__ __forceinline__ bool tone_omega(const float (&v)[L], float cw, float 
     if (odd) s0 = fmaf(v[m], 1.f / kSqrt2, s0);
     const float a = s1 * frcp(s2);                              // -h_1 / h_2
     if (!(s0 * s2 > 0.f && fabsf(a) <= 0.25f)) return false;
-    // x and y at w + a
-    {
-        const float al = odd ? a : 0.5f * a, a2 = al * al;
-        const float c1 = fmaf(a2, fmaf(a2, fmaf(a2, -1.f / 720.f, 1.f / 24.f), -0.5f), 1.f);
-        const float d1 = al * fmaf(a2, fmaf(a2, 1.f / 120.f, -1.f / 6.f), 1.f);
-        const float c2 = odd ? c1 : fmaf(c1, c1, -d1 * d1), d2 = odd ? d1 : 2.f * c1 * d1;
-        float cr = c1, ci = d1;
+    float off = a, step = a;                                    // the point of the expansion: w + off
+#pragma unroll 1
+    for (bool more = AGAIN;; more = false) {
+        // x and y at the point
+        {
+            const float al = odd ? step : 0.5f * step, a2 = al * al;
+            const float c1 = fmaf(a2, fmaf(a2, fmaf(a2, -1.f / 720.f, 1.f / 24.f), -0.5f), 1.f);
+            const float d1 = al * fmaf(a2, fmaf(a2, 1.f / 120.f, -1.f / 6.f), 1.f);
+            const float c2 = odd ? c1 : fmaf(c1, c1, -d1 * d1), d2 = odd ? d1 : 2.f * c1 * d1;
+            float cr = c1, ci = d1;
 #pragma unroll
-        for (int i = m - 1; i >= 0; --i) {
-            const float xn = fmaf(x[i], cr, y[i] * ci);
-            y[i] = fmaf(y[i], cr, -x[i] * ci);
-            x[i] = xn;
-            if (i > 0) {
-                const float t = fmaf(cr, c2, -ci * d2);
-                ci = fmaf(cr, d2, ci * c2);
-                cr = t;
+            for (int i = m - 1; i >= 0; --i) {
+                const float xn = fmaf(x[i], cr, y[i] * ci);
+                y[i] = fmaf(y[i], cr, -x[i] * ci);
+                x[i] = xn;
+                if (i > 0) {
+                    const float t = fmaf(cr, c2, -ci * d2);
+                    ci = fmaf(cr, d2, ci * c2);
+                    cr = t;
+                }
             }
         }
-    }
-    float h0 = 0.f, h1 = 0.f, h2 = 0.f, h3 = 0.f, h4 = 0.f, h5 = 0.f;
+        float h0 = 0.f, h1 = 0.f, h2 = 0.f, h3 = 0.f, h4 = 0.f, h5 = 0.f;
 #pragma unroll
-    for (int i = 0; i < m; ++i) {
-        const float k = kk(i), k2 = k * k, k3 = k2 * k;
-        h0 += x[i];
-        h1 = fmaf(k, y[i], h1);
-        h2 = fmaf(-k2, x[i], h2);
-        h3 = fmaf(-k3, y[i], h3);
-        h4 = fmaf(k2 * k2, x[i], h4);
-        h5 = fmaf(k3 * k2, y[i], h5);
+        for (int i = 0; i < m; ++i) {
+            const float k = kk(i), k2 = k * k, k3 = k2 * k;
+            h0 += x[i];
+            h1 = fmaf(k, y[i], h1);
+            h2 = fmaf(-k2, x[i], h2);
+            h3 = fmaf(-k3, y[i], h3);
+            h4 = fmaf(k2 * k2, x[i], h4);
+            h5 = fmaf(k3 * k2, y[i], h5);
+        }
+        if (odd) h0 = fmaf(v[m], 1.f / kSqrt2, h0);
+        // all moments lack the factor sqrt2 (and g's sign, which the ratios drop)
+        const float sg = h0 < 0.f ? -1.f : 1.f;
+        const float dl = fmaf(-kSqrt2, fabsf(h0), sqrtf((float)L)) * (sg / kSqrt2);
+        const float ih2 = frcp(h2);
+        float T = -2.f * dl * ih2;
+        T = -2.f * fmaf(-h4 * (1.f / 24.f), T * T, dl) * ih2;
+        const float q = fmaf(fmaf(h5 * (-1.f / 120.f), T, h3 * (1.f / 6.f)), T, -h1);
+        const float iD = frcp(fmaf(-h4 * (1.f / 6.f), T, h2));
+        float xx = q * iD;
+        xx = fmaf(-0.5f * h3 * xx, xx, q) * iD;
+        if (!(fmaf(-2.f * h0, h0, (float)L) <= tone_s2(L) * (float)L && kmax * kmax * fabsf(T) <= 0.2f &&
+              fabsf(xx) <= (more ? 0.02f : 3e-4f)))
+            return false;
+        off += xx;
+        if (!more || fabsf(xx) <= 3e-4f) break;
+        step = xx;
     }
-    if (odd) h0 = fmaf(v[m], 1.f / kSqrt2, h0);
-    // all moments lack the factor sqrt2 (and g's sign, which the ratios drop)
-    const float sg = h0 < 0.f ? -1.f : 1.f;
-    const float dl = fmaf(-kSqrt2, fabsf(h0), sqrtf((float)L)) * (sg / kSqrt2);
-    const float ih2 = frcp(h2);
-    float T = -2.f * dl * ih2;
-    T = -2.f * fmaf(-h4 * (1.f / 24.f), T * T, dl) * ih2;
-    const float q = fmaf(fmaf(h5 * (-1.f / 120.f), T, h3 * (1.f / 6.f)), T, -h1);
-    const float iD = frcp(fmaf(-h4 * (1.f / 6.f), T, h2));
-    float xx = q * iD;
-    xx = fmaf(-0.5f * h3 * xx, xx, q) * iD;
-    if (!(fmaf(-2.f * h0, h0, (float)L) <= tone_s2(L) * (float)L && fabsf(xx) <= 3e-4f && kmax * kmax * fabsf(T) <= 0.2f))
-        return false;
     constexpr float kPi = 3.14159265358979324f;
-    const float w = atan2f((float)Ei, (float)Er) + (a + xx);
+    const float w = atan2f((float)Ei, (float)Er) + off;
     omega = w > kPi ? w - 2.f * kPi : (w < -kPi ? w + 2.f * kPi : w);
     return true;
 }
@@ -1547,6 +1566,15 @@ constexpr int kPowerMinSteps = 2;
 constexpr int kPowerMaxSteps = 8;
 constexpr float kPowerTol = 6e-6f;
 constexpr float kPowerTolBlock = 4e-6f;
+// At most sixteen for blocks of 9 x 9 to 15 x 15, where a window given up waits for
+// another kernel: host trials, windows left after 8 and 16 steps and steps of a
+// wave's slowest lane, 9 x 9 at 3 dB 1070 and 23 of 12000, 7.0 and 8.4; 15 x 15 at 3
+// dB 878 and 22, 6.1 and 6.7; 9 x 9 at 0 dB 9876 and 3434, 7.0 and 10.3.  2 x 1024^2
+// at 3 dB 424 -> 334 us (9 x 9), 884 -> 743 (15 x 15), at 0 dB 1297 -> 1088, the second
+// expansion of tone_omega included.  17 x 17 windows bend more: on frames of few
+// lines those that need more steps are not one tone either, and the steps only add
+// to the path (500 x 64: 97 us against 87).
+constexpr int power_max_steps_big(int L) { return L <= 15 ? 16 : kPowerMaxSteps; }
 
 // The signal eigenvector of T by the tridiagonal solver (Jacobi with
 // JACOBI); false, with BM_FLAG_DEGENERATE, when the subspace is not determined.

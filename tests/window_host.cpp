@@ -25,13 +25,14 @@ using namespace bm;
 
 namespace {
 
-// tone_omega of n signal vectors from the directions (cw, sw).
+// tone_omega of n signal vectors from the directions (cw, sw), above L = 8 as the tile
+// kernel of block windows calls it.
 template <int L>
 void tone(const float* v, const float* cw, const float* sw, int n, float* omega, uint8_t* ok) {
     for (int q = 0; q < n; ++q) {
         float a[L], w = NAN;
         std::memcpy(a, v + (int64_t)q * L, sizeof a);
-        ok[q] = tone_omega<L>(a, cw[q], sw[q], w);
+        ok[q] = tone_omega<L, (L > kMaxL)>(a, cw[q], sw[q], w);
         omega[q] = w;
     }
 }
