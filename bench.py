@@ -4,7 +4,8 @@
 Workload (default, cfg4): 16 time-lapsed 4096x4096 fringe frames stored FP16,
 carrier 1/8 cyc/px at 45 degrees, erf diffusion phase, SNR 10 dB; local
 frequency along x and y with windows of N=32 samples and L=8 covariances
-(FP32 covariance, eigen-split and rooting, FP64 root polish), then FP64
+(FP32 covariance, eigen-split and root pair, the pair's direction in FP64;
+FP64 Newton steps where the closed-form pair does not serve), then FP64
 integration of both maps to phase.  One step = one bosmusic_demodulate call
 over all frames plus the integration of every frame, inputs resident in HBM.
 The same frames are timed twice: with the plain root-MUSIC path (the line's
@@ -349,8 +350,8 @@ def workload(name, nframes):
     elif name in ("cfg4", "cfg5"):
         fr = [wl.cfg4_frame(t) for t in range(nframes or 16)]
         desc = (f"{len(fr)} time-lapsed 4096x4096 fringe frames stored FP16, carrier 1/8 cyc/px at 45 deg, 6*erf "
-                f"diffusion phase, SNR 10 dB; x and y windows N=32, L=8; FP32 covariance/eigen/rooting, FP64 "
-                f"root polish and phase prefix sums. Plain root-MUSIC (value) vs surrogate MLP 32-64-64-2 "
+                f"diffusion phase, SNR 10 dB; x and y windows N=32, L=8; FP32 covariance/eigen/root pair, its "
+                f"direction and the phase prefix sums in FP64. Plain root-MUSIC (value) vs surrogate MLP 32-64-64-2 "
                 f"(GELU, BF16 MFMA, FP32 accumulate) trained on the GPU on 10M method-generated windows "
                 f"(carrier 1/16-1/4 cyc/px, SNR 0-30 dB, root-MUSIC L=8 N=32 labels) seeding a verified power "
                 f"iteration for the signal eigenvector, plain eigen-split where it does not serve (surrogate)")
@@ -388,8 +389,9 @@ def main():
     ap.add_argument("--full-roots", action="store_true",
                     help="find every root of every window (no certified-pair shortcut)")
     ap.add_argument("--warm", action="store_true",
-                    help="temporal warm start: frame t starts its Newton iterations at frame t-1's maps "
-                         "(computed before the timed steps, as a streaming pipeline would have them)")
+                    help="temporal warm start: windows that the closed form does not serve start their Newton "
+                         "iterations at frame t-1's maps (computed before the timed steps, as a streaming "
+                         "pipeline would have them)")
     ap.add_argument("--copy-mib", type=int, default=0,
                     help="run one plain device copy of this many MiB first (HBM counter calibration)")
     args = ap.parse_args()

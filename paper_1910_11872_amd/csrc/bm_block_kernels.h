@@ -15,14 +15,13 @@
 // What bounds it: VALU issue, with the LDS reads of the lag sums (L (L+1)/2
 // per window and direction) beside it at about half their rate's limit.
 // Measured against summing each window's T from its own snapshots, on 20
-// frames of 1024 x 1024 with 11 x 11 blocks 4.25 -> 1.74 ms, one 1850 x 700
-// frame with 15 x 15 blocks and the phase 0.96 -> 0.29 (all the call's launches).
-// The
-// eigen-split's real symmetric T holds L (L+1)/2 registers, so the sizes above
-// 8 x 8 keep only the common route in this kernel (power iteration, then the
-// closed form of a window close to one tone): at two to four waves per SIMD
-// they hide the LDS latency that the one wave of the whole method's 512
-// registers cannot.  A window that this route does not prove gets a NaN of its
+// frames of 1024 x 1024 with 11 x 11 blocks 4.25 -> 1.58 ms, one 1850 x 700
+// frame with 15 x 15 blocks and the phase 0.96 -> 0.26 (all the call's launches).
+// The eigen-split's real symmetric T holds L (L+1)/2 registers, so the sizes
+// above 8 x 8 keep only the common route in this kernel (power iteration, then
+// the closed form of a window close to one tone, with its second expansion): at
+// two to four waves per SIMD they hide the LDS latency that the one wave of the
+// whole method's 512 registers cannot.  A window that this route does not prove gets a NaN of its
 // own payload in its map, and block_rest_kernel, launched behind on the same
 // stream, finishes exactly those with every other solver.  Up to 8 x 8 the
 // whole method fits beside it and each lane finishes its window itself.
@@ -408,7 +407,9 @@ void block_tile_kernel(RmBatch B) {
 // takes up to kRestTiles tiles, looks their places up once and reads the maps
 // of kRestScan tiles together: against four tiles a pass, each looked up and
 // read in turn, 20 x 1024^2 at 10 dB with 9 x 9 blocks 1.57 -> 1.46 ms, 11 x 11
-// 1.80 -> 1.75, 4 x 1024^2 at 3 dB 0.97 -> 0.94, one 1850 x 700 frame 164 -> 157 us.
+// 1.80 -> 1.75, 4 x 1024^2 at 3 dB 0.97 -> 0.94, one 1850 x 700 frame 164 -> 157 us
+// (with the windows that the tile kernel left before its second expansion; now the
+// pass finds next to nothing in the first two and takes 4 us).
 constexpr int kRestTiles = 16;
 constexpr int kRestScan = 4;           // marked tiles whose maps are read together
 constexpr int kRestChunk = 4;          // neighbouring tiles of a block's chunk

@@ -1573,7 +1573,7 @@ constexpr float kPowerTolBlock = 4e-6f;
 // at 3 dB 424 -> 334 us (9 x 9), 884 -> 743 (15 x 15), at 0 dB 1297 -> 1088, the second
 // expansion of tone_omega included.  17 x 17 windows bend more: on frames of few
 // lines those that need more steps are not one tone either, and the steps only add
-// to the path (500 x 64: 97 us against 87).
+// to the path (500 x 64: 98 us against 90).
 constexpr int power_max_steps_big(int L) { return L <= 15 ? 16 : kPowerMaxSteps; }
 
 // The signal eigenvector of T by the tridiagonal solver (Jacobi with
